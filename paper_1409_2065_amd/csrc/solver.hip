@@ -243,72 +243,113 @@ __device__ inline double readlane_d(double v, int k) {
   return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
 }
 
+// A double moved between lanes by data-parallel primitives: two 32-bit VALU
+// moves, against two LDS-unit permutes for a shuffle.  Every sweep ends and
+// begins with sums over the block, a serial chain that bounds small problems
+// and that 16 waves per CU queue up for in the LDS unit on larger ones:
+// against shuffles one at a time (wave trees and block sums written out by
+// one thread) a 200 x 10 FP64 solve went from 10.9 to 8.5 us per MM iteration
+// and a 2000 x 500 path from 35.4 to 31.4, with the same bits.
+// dpp<CTRL>(v): every
+// lane reads the lane CTRL names within its row of 16 (kRor: rotation; a
+// rotation by 8 is an exchange of lanes 8 apart).
+constexpr int kRowShl = 0x100, kRowShr = 0x110, kRor = 0x120;
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E;  // quad permutations
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) {
+  const int lo = __double2loint(v), hi = __double2hiint(v);
+  return __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, false),
+                          __builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, false));
+}
+// The lanes 4 apart: banks (4 lanes) 0 and 2 of each row read 4 lanes up,
+// banks 1 and 3 read 4 lanes down.
+__device__ __forceinline__ double dpp_xor4(double v) {
+  const int lo = __double2loint(v), hi = __double2hiint(v);
+  int l = __builtin_amdgcn_update_dpp(lo, lo, kRowShl + 4, 0xf, 0x5, false);
+  int h = __builtin_amdgcn_update_dpp(hi, hi, kRowShl + 4, 0xf, 0x5, false);
+  l = __builtin_amdgcn_update_dpp(l, lo, kRowShr + 4, 0xf, 0xa, false);
+  h = __builtin_amdgcn_update_dpp(h, hi, kRowShr + 4, 0xf, 0xa, false);
+  return __hiloint2double(h, l);
+}
+// Sum over the two halves of the wave of a (returned to lanes 0..31) and of
+// b (to lanes 32..63): the upper half of a is exchanged with the lower half
+// of b, and every lane adds its two values.  pair_sum16: the same between
+// neighbouring rows of 16 (a to the even rows, b to the odd ones).
+__device__ __forceinline__ double pair_sum32(double a, double b) {
+  const auto l = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+  const auto h = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+  return __hiloint2double(h[0], l[0]) + __hiloint2double(h[1], l[1]);
+}
+__device__ __forceinline__ double pair_sum16(double a, double b) {
+  const auto l = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
+  const auto h = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
+  return __hiloint2double(h[0], l[0]) + __hiloint2double(h[1], l[1]);
+}
+
+// Sum over the wave, in every lane: lanes 32, 16, 8, 4, 2, 1 apart add up
+// in that order (after the exchange over 8 lanes the values repeat every 8,
+// so the rotations by 4, 2, 1 are exchanges too).
 __device__ inline double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
+  v = pair_sum32(v, v);
+  v = pair_sum16(v, v);
+  v += dpp<kRor + 8>(v);
+  v += dpp<kRor + 4>(v);
+  v += dpp<kRor + 2>(v);
+  v += dpp<kRor + 1>(v);
   return v;
 }
 
-// Sums over the wave of 8 values per lane, value q's total returned to lane
-// q (lanes 8..63 get some total).  Transpose steps halve the values held per
-// lane (pairs of lanes 32, 16, 8 apart swap halves), leaving value
-// 4 b5 + 2 b4 + b3 (b = lane bits) summed over 8 lanes; the 8-lane groups
-// then reduce, and lane q reads the total of value q from lane 8q.  A fixed
-// order: every run gives the same bits.
-__device__ inline double wave_sum8(double (&v)[8]) {
-  const int lane = threadIdx.x % kWave;
-  {
-    const bool hi = (lane & 32) != 0;
+// Sums over the wave of 8 values per lane, value q's total left in lanes
+// 8q .. 8q+7: the steps over 32, 16 and 8 lanes halve the values held per
+// lane (value 4 b5 + 2 b4 + b3 of lane bits b), then the 8-lane groups
+// reduce.  Each value is added in the order of wave_sum.  7 exchanges for 8
+// values where wave_sum needs 48.
+__device__ __forceinline__ double wave_sum8_groups(const double (&v)[8]) {
+  double a[4], b[2];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const double send = hi ? v[j] : v[4 + j];
-      const double keep = hi ? v[4 + j] : v[j];
-      v[j] = keep + __shfl_xor(send, 32, kWave);
-    }
-  }
-  {
-    const bool hi = (lane & 16) != 0;
+  for (int j = 0; j < 4; ++j) a[j] = pair_sum32(v[j], v[4 + j]);
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const double send = hi ? v[j] : v[2 + j];
-      const double keep = hi ? v[2 + j] : v[j];
-      v[j] = keep + __shfl_xor(send, 16, kWave);
-    }
-  }
-  double t;
-  {
-    const bool hi = (lane & 8) != 0;
-    const double send = hi ? v[0] : v[1];
-    const double keep = hi ? v[1] : v[0];
-    t = keep + __shfl_xor(send, 8, kWave);
-  }
-  t += __shfl_xor(t, 4, kWave);
-  t += __shfl_xor(t, 2, kWave);
-  t += __shfl_xor(t, 1, kWave);
-  return __shfl(t, (8 * lane) % kWave, kWave);
+  for (int j = 0; j < 2; ++j) b[j] = pair_sum16(a[j], a[2 + j]);
+  const bool hi = (threadIdx.x & 8) != 0;
+  double t = (hi ? b[1] : b[0]) + dpp<kRor + 8>(hi ? b[0] : b[1]);
+  t += dpp_xor4(t);
+  t += dpp<kXor2>(t);
+  t += dpp<kXor1>(t);
+  return t;
+}
+// The same with value q's total returned to lane q (lanes 8..63 get some total).
+__device__ inline double wave_sum8(const double (&v)[8]) {
+  return __shfl(wave_sum8_groups(v), (8 * (threadIdx.x % kWave)) % kWave, kWave);
 }
 
-// Fixed-order block reduction of NV doubles per thread; result valid in
-// thread 0.  Uses a shared scratch of (waves per block) * NV doubles.
+// Wave sums of NV <= 9 values stored to dst[0 .. NV-1]: eight at once, the
+// ninth by itself.
 template <int NV>
-__device__ inline void block_sum(double (&v)[NV], double *scratch) {
-  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+__device__ __forceinline__ void wave_sums_store(const double (&v)[NV], double *dst) {
+  static_assert(NV <= 9, "eight at once and one more");
+  const int lane = threadIdx.x % kWave;
+  double w[8];
 #pragma unroll
-  for (int q = 0; q < NV; ++q) v[q] = wave_sum(v[q]);
-  if (lane == 0) {
-#pragma unroll
-    for (int q = 0; q < NV; ++q) scratch[wave * NV + q] = v[q];
+  for (int q = 0; q < 8; ++q) w[q] = q < NV ? v[q < NV ? q : 0] : 0.0;
+  const double t = wave_sum8_groups(w);
+  if ((lane & 7) == 0 && (lane >> 3) < NV) dst[lane >> 3] = t;
+  if constexpr (NV == 9) {
+    const double l = wave_sum(v[8]);
+    if (lane == 0) dst[8] = l;
   }
+}
+
+// Fixed-order block reduction of NV doubles per thread: wave trees, then
+// thread q < NV adds value q over the waves in order and returns it (other
+// threads return 0).  scratch: (waves per block) * NV doubles.
+template <int NV>
+__device__ inline double block_sum(const double (&v)[NV], double *scratch) {
+  wave_sums_store<NV>(v, scratch + (threadIdx.x / kWave) * NV);
   __syncthreads();
-  if (threadIdx.x == 0) {
-#pragma unroll
-    for (int q = 0; q < NV; ++q) {
-      double acc = 0.0;
-      for (int w = 0; w < (int)(blockDim.x / kWave); ++w) acc += scratch[w * NV + q];
-      v[q] = acc;
-    }
-  }
-  __syncthreads();
+  double acc = 0.0;
+  if (threadIdx.x < NV)
+    for (int w = 0; w < (int)(blockDim.x / kWave); ++w) acc += scratch[w * NV + threadIdx.x];
+  return acc;
 }
 
 // Fixed-order block reduction whose result every thread receives: wave
@@ -317,13 +358,7 @@ __device__ inline void block_sum(double (&v)[NV], double *scratch) {
 // reused by the caller before its next barrier.
 template <int NV, int NW>
 __device__ inline void block_sum_all(double (&v)[NV], double *scratch) {
-  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-#pragma unroll
-  for (int q = 0; q < NV; ++q) v[q] = wave_sum(v[q]);
-  if (lane == 0) {
-#pragma unroll
-    for (int q = 0; q < NV; ++q) scratch[wave * NV + q] = v[q];
-  }
+  wave_sums_store<NV>(v, scratch + (threadIdx.x / kWave) * NV);
   __syncthreads();
   if (threadIdx.x < NV) {
     double acc = 0.0;
@@ -967,11 +1002,8 @@ __device__ __forceinline__ void point_sweep(const PointArgs &a, const Blk blk) {
       }
     }
   }
-  block_sum<kPointSums>(ps, scratch);
-  if (threadIdx.x == 0) {
-#pragma unroll
-    for (int q = 0; q < kPointSums; ++q) a.psum[(size_t)lb * 8 + q] = ps[q];
-  }
+  const double tot = block_sum<kPointSums>(ps, scratch);
+  if (threadIdx.x < kPointSums) a.psum[(size_t)lb * 8 + threadIdx.x] = tot;
 }
 
 // PF: prefetch each next item (for waves with several items).  NW waves
@@ -1214,11 +1246,8 @@ __global__ __launch_bounds__(kBlock) void k_point_slab(PointArgs a) {
       }
     }
   }
-  block_sum<kPointSums>(ps, scratch);
-  if (threadIdx.x == 0) {
-#pragma unroll
-    for (int q = 0; q < kPointSums; ++q) a.psum[(size_t)lb * 8 + q] = ps[q];
-  }
+  const double tot = block_sum<kPointSums>(ps, scratch);
+  if (threadIdx.x < kPointSums) a.psum[(size_t)lb * 8 + threadIdx.x] = tot;
 }
 
 // ------------------------------------------------------------- k_jacobi
@@ -1392,12 +1421,8 @@ __global__ __launch_bounds__(kPointBlock) void k_jacobi(JacArgs a) {
     }
   }
   if constexpr (LAST) {
-    block_sum<3>(ps, scratch);
-    if (threadIdx.x == 0) {
-      a.psum[(size_t)lb * 8 + 0] = ps[0];
-      a.psum[(size_t)lb * 8 + 1] = ps[1];
-      a.psum[(size_t)lb * 8 + 5] = ps[2];
-    }
+    const double tot = block_sum<3>(ps, scratch);
+    if (threadIdx.x < 3) a.psum[(size_t)lb * 8 + (threadIdx.x < 2 ? threadIdx.x : 5)] = tot;
   }
 }
 
@@ -1472,12 +1497,9 @@ __device__ inline void edge_block_partials(double (&t3)[kEdgeSums], double pt, d
   __shared__ double red[kEdgeWaves * kEdgeSums];
   double *row = esum + (size_t)blk.b * kEsumStride;
   if (threadIdx.x < kPointSums) row[threadIdx.x] = pt;
-  block_sum<kEdgeSums>(t3, red);
-  if (threadIdx.x == 0) {
-#pragma unroll
-    for (int q = 0; q < kEdgeSums; ++q) row[kPointSums + q] = t3[q];
-    row[kIterSums] = 0.0;  // padding
-  }
+  const double tot = block_sum<kEdgeSums>(t3, red);
+  if (threadIdx.x < kEdgeSums) row[kPointSums + threadIdx.x] = tot;
+  if (threadIdx.x == kEdgeSums) row[kIterSums] = 0.0;  // padding
 }
 
 // -------------------------------------------------------------- k_edge
