@@ -313,6 +313,12 @@ cc_status batch_run(Batch *B, int32_t *labels, cc_solve_info *infos, double *lat
 void batch_free(Batch *B);
 
 // ---- weights and preparation (knn.hip) ----
+// Observed column means and, where sec is not null, the sums of squared
+// deviations (root: their root mean square); adds the number of non-finite
+// observed entries to *nonfinite (may be NULL), skip leaves them out.
+void column_moments(int64_t n, int64_t p, int32_t x_dtype, const void *X, int64_t ldx, const uint8_t *mask,
+                    int64_t ldm, bool skip, double *mean, double *sec, bool root, int *nonfinite,
+                    hipStream_t stream);
 cc_status build_knn_weights(int64_t n, int64_t p, int32_t x_dtype,
                             const void *X, int64_t ldx, const uint8_t *mask,
                             int64_t ldm, int32_t k, double phi,

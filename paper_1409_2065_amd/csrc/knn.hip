@@ -6,9 +6,9 @@
 //      them, kept in FP32 (for ranking) and FP64 (for exact distances);
 //   2. Gram matrix G = X~ X~^T on the matrix cores (v_mfma_f32_16x16x4_f32),
 //      d2_ij = |x_i|^2 + |x_j|^2 - 2 G_ij in FP32 for every pair;
-//   3. per row, a bitonic sort in LDS of (d2, j) keys, self excluded, ties to
-//      the lower index, keeps the K = k + margin best candidates;
-//   4. exact FP64 distances of the candidates, re-sorted by (d2, j), keep k;
+//   3. per row, a selection in registers of the K = k + margin smallest
+//      (d2, j) pairs, self excluded, ties to the lower index;
+//   4. exact FP64 distances of the candidates, ranked by (d2, j), keep k;
 //   5. the relation i ~_k j (either direction) as a bitmap, counted and
 //      prefix-summed per row, written out as sorted edges (i < j);
 //   6. exact FP64 d2 per edge, phi (literal or |phi| / lower median d2),
@@ -32,30 +32,108 @@ namespace ccmi {
 static inline int64_t cdiv64(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // ---------------------------------------------------------- column stats
-template <typename TI>
-__global__ void k_col_moments(int n, int p, const TI *X, int64_t ldx, const uint8_t *M,
-                              int64_t ldm, double *mean, double *sd, int *nonfinite) {
-  const int f = blockIdx.x * blockDim.x + threadIdx.x;
-  if (f >= p) return;
+// Per column over its observed entries: the mean, and (sec not null) the
+// sum of squared deviations from it or its root mean square; the count of
+// non-finite observed entries is added to *nonfinite, and with skip they are
+// left out of the sums.  A block of 1024 threads owns CPB columns, so a
+// column's rows are read by 1024 / CPB threads at once, 8 rows of each in
+// flight, and both passes (mean, then deviations) run in one launch without
+// workspace.  A thread per column instead waits on one row after another:
+// 1550 us on 2000 x 500 with a mask and 5900 us on 12000 x 64, against 10
+// and 20 us here.  Narrow matrices take 4 columns per block so that more
+// than a few blocks share the rows; from 1024 columns on, 16 (64 bytes of
+// each FP32 row) already fill the chip.
+constexpr int kColRows = 8;  // rows a thread has in flight
+
+template <typename TI, int CPB>
+__global__ __launch_bounds__(1024) void k_col_moments(int n, int p, const TI *X, int64_t ldx, const uint8_t *M,
+                                                      int64_t ldm, int skip, double *mean, double *sec, int root,
+                                                      int *nonfinite) {
+  constexpr int RG = 1024 / CPB, NW = 1024 / kWave;
+  __shared__ double ssum[NW][CPB];
+  __shared__ int scnt[NW][CPB];
+  __shared__ int sbad;
+  const int c = threadIdx.x % CPB, g = threadIdx.x / CPB, wave = threadIdx.x / kWave;
+  const int f = blockIdx.x * CPB + c;
+  const bool col = f < p;
+  const int fc = col ? f : 0;
+  if (threadIdx.x == 0) sbad = 0;
+  // fn(x) for every row of this thread that counts; returns the bad ones
+  auto rows = [&](auto fn) {
+    int bad = 0;
+    for (int i0 = g; i0 < n; i0 += RG * kColRows) {
+      TI x[kColRows];
+      uint8_t o[kColRows];
+#pragma unroll
+      for (int u = 0; u < kColRows; ++u) {
+        const int i = min(i0 + u * RG, n - 1);
+        o[u] = M ? M[(size_t)i * ldm + fc] : (uint8_t)1;
+        x[u] = X[(size_t)i * ldx + fc];
+      }
+#pragma unroll
+      for (int u = 0; u < kColRows; ++u) {
+        if (i0 + u * RG >= n || o[u] == 0) continue;
+        const bool fin = isfinite((double)x[u]);
+        if (!fin) ++bad;
+        if (fin || !skip) fn((double)x[u]);
+      }
+    }
+    return bad;
+  };
+  // column totals of a value per thread within a wave: lanes
+  // CPB apart
+  auto lanes = [&](auto v) {
+#pragma unroll
+    for (int off = kWave / 2; off >= CPB; off >>= 1) v += __shfl_xor(v, off, kWave);
+    return v;
+  };
   double sum = 0.0;
-  int cnt = 0, bad = 0;
-  for (int i = 0; i < n; ++i) {
-    if (M && M[(size_t)i * ldm + f] == 0) continue;
-    const double x = (double)X[(size_t)i * ldx + f];
-    if (!isfinite(x)) { ++bad; continue; }
-    sum += x; ++cnt;
-  }
-  const double mu = cnt > 0 ? sum / cnt : 0.0;
+  int cnt = 0;
+  const int bad = rows([&](double x) { sum += x; ++cnt; });
+  sum = lanes(sum);
+  cnt = lanes(cnt);
+  if (threadIdx.x % kWave < CPB) { ssum[wave][c] = sum; scnt[wave][c] = cnt; }
+  __syncthreads();
+  if (bad && col) atomicAdd(&sbad, bad);
+  int tc = 0;
+  double mu = 0.0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) { mu += ssum[w][c]; tc += scnt[w][c]; }
+  mu = tc > 0 ? mu / tc : 0.0;
+  if (threadIdx.x < CPB && col) mean[f] = mu;
+  __syncthreads();
+  if (threadIdx.x == 0 && sbad && nonfinite) atomicAdd(nonfinite, sbad);
+  if (!sec) return;
   double ss = 0.0;
-  for (int i = 0; i < n; ++i) {
-    if (M && M[(size_t)i * ldm + f] == 0) continue;
-    const double x = (double)X[(size_t)i * ldx + f];
-    if (!isfinite(x)) continue;
-    ss += (x - mu) * (x - mu);
+  rows([&](double x) { ss += (x - mu) * (x - mu); });
+  ss = lanes(ss);
+  if (threadIdx.x % kWave < CPB) ssum[wave][c] = ss;
+  __syncthreads();
+  if (threadIdx.x < CPB && col) {
+    double t = 0.0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) t += ssum[w][c];
+    sec[f] = root ? (tc > 0 ? sqrt(t / tc) : 0.0) : t;
   }
-  mean[f] = mu;
-  if (sd) sd[f] = cnt > 0 ? sqrt(ss / cnt) : 0.0;
-  if (bad) atomicAdd(nonfinite, bad);
+}
+
+template <typename TI>
+static void moments_launch(int64_t n, int64_t p, const TI *X, int64_t ldx, const uint8_t *M, int64_t ldm, bool skip,
+                           double *mean, double *sec, bool root, int *nonfinite, hipStream_t st) {
+  if (p <= 1024)
+    hipLaunchKernelGGL((k_col_moments<TI, 4>), dim3((int)cdiv64(p, 4)), dim3(1024), 0, st, (int)n, (int)p, X, ldx, M,
+                       ldm, skip ? 1 : 0, mean, sec, root ? 1 : 0, nonfinite);
+  else
+    hipLaunchKernelGGL((k_col_moments<TI, 16>), dim3((int)cdiv64(p, 16)), dim3(1024), 0, st, (int)n, (int)p, X, ldx,
+                       M, ldm, skip ? 1 : 0, mean, sec, root ? 1 : 0, nonfinite);
+}
+
+void column_moments(int64_t n, int64_t p, int32_t x_dtype, const void *X, int64_t ldx, const uint8_t *mask,
+                    int64_t ldm, bool skip, double *mean, double *sec, bool root, int *nonfinite, hipStream_t st) {
+  if (x_dtype == CC_DTYPE_F32)
+    moments_launch(n, p, (const float *)X, ldx, mask, ldm, skip, mean, sec, root, nonfinite, st);
+  else
+    moments_launch(n, p, (const double *)X, ldx, mask, ldm, skip, mean, sec, root, nonfinite, st);
 }
 
 template <typename TI>
@@ -116,17 +194,18 @@ __global__ void k_rownorm(int n_pad, int ldk, const float *Xf, float *nrm) {
 // result register r of lane l holds (row 4*(l/16)+r, col l%16).
 // When the output tiles alone cannot fill the chip, blockIdx.z splits K:
 // each split writes its partial tile to part, and k_gram_combine adds the
-// splits in a fixed order.
+// splits in a fixed order.  D2 and part hold the rows from row0 on (a panel
+// of the matrix; rows_pad of them with padding).
 constexpr int kGT = 64, kKC = 32;
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 __global__ __launch_bounds__(256) void k_gram_d2(int n, int n_pad, int ldk, int nsplit,
-                                                 const float *Xf, const float *nrm, float *D2,
-                                                 int64_t ldd, float *part) {
+                                                 const float *Xf, const float *nrm, int row0,
+                                                 int rows_pad, float *D2, int64_t ldd, float *part) {
   __shared__ float As[kGT][kKC + 1];
   __shared__ float Bs[kGT][kKC + 1];
-  const int bi = blockIdx.y * kGT, bj = blockIdx.x * kGT;
+  const int bi = row0 + blockIdx.y * kGT, bj = blockIdx.x * kGT;
   const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
   const int nch = ldk / kKC;
   const int per = (nch + nsplit - 1) / nsplit;
@@ -174,22 +253,22 @@ __global__ __launch_bounds__(256) void k_gram_d2(int n, int n_pad, int ldk, int 
       const int i = bi + wave * 16 + 4 * (lane / 16) + q;
       const int j = bj + c * 16 + lane % 16;
       if (nsplit > 1)
-        part[((size_t)blockIdx.z * n_pad + i) * n_pad + j] = acc[c][q];
+        part[((size_t)blockIdx.z * rows_pad + (i - row0)) * n_pad + j] = acc[c][q];
       else if (i < n && j < n)
-        D2[(size_t)i * ldd + j] = nrm[i] + nrm[j] - 2.0f * acc[c][q];
+        D2[(size_t)(i - row0) * ldd + j] = nrm[i] + nrm[j] - 2.0f * acc[c][q];
     }
   }
 }
 
 // d2 from the K-split partial Gram tiles, splits added in order.
 __global__ void k_gram_combine(int n, int n_pad, int nsplit, const float *part, const float *nrm,
-                               float *D2, int64_t ldd) {
+                               int row0, int rows, int rows_pad, float *D2, int64_t ldd) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= (int64_t)n * n) return;
-  const int i = (int)(e / n), j = (int)(e - (int64_t)i * n);
+  if (e >= (int64_t)rows * n) return;
+  const int r = (int)(e / n), j = (int)(e - (int64_t)r * n);
   float g = 0.f;
-  for (int z = 0; z < nsplit; ++z) g += part[((size_t)z * n_pad + i) * n_pad + j];
-  D2[(size_t)i * ldd + j] = nrm[i] + nrm[j] - 2.0f * g;
+  for (int z = 0; z < nsplit; ++z) g += part[((size_t)z * rows_pad + r) * n_pad + j];
+  D2[(size_t)r * ldd + j] = nrm[row0 + r] + nrm[j] - 2.0f * g;
 }
 
 // Monotone map of a float to an unsigned key (handles negative values).
@@ -199,44 +278,180 @@ __device__ inline uint32_t float_key(float f) {
 }
 
 // Most candidates k_recheck takes per row (12 bytes of LDS each), and the
-// largest n of the kNN builders (a row's sort keys fill 8 * n bytes of LDS).
+// largest n of the kNN builders (a row's keys fill the registers of a block).
 constexpr int64_t kRecheckMaxK = 12288;
 constexpr int64_t kKnnMaxN = 16384;
+static_assert(kKnnMaxN <= 64 * 256, "64 keys per thread in k_row_select");
+// Largest panel of the distance matrix kept at once: it stays in the last
+// level cache between the product that writes it and the selection that
+// reads it, and a build of 12000 rows holds 64 MiB instead of 576.
+constexpr int64_t kPanelBytes = (int64_t)64 << 20;
 
 // Inverse of float_key.
 __device__ inline float key_float(uint32_t k) {
   return __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
 }
 
-// Per row: bitonic sort of (key(d2) << 32 | j) in LDS; keep the first K, and
-// in dnext the FP32 d2 of the first row left out (infinity when none is).
+// Per row: the K smallest (d2, j) pairs over the other rows j (in no
+// particular order), and in dnext the FP32 d2 of the first one left out
+// (infinity when none is).  Row r of the panel D2 is row row0 + r.  A block
+// of 4 waves holds the row's keys in registers, PT per thread.  A K-th
+// smallest key is built two bits at a time, as the largest v with fewer than
+// K keys below it: a step counts the keys below three trial values with
+// ballots and one barrier.
+// The K-th smallest of the 256 threads' smallest keys bounds the row's K-th
+// smallest from above, and little more than K keys lie below that bound: they
+// go to LDS and are ranked there, by (key, j).  Only a row with more than
+// kSelList such keys (K near 256 or above, many ties) takes the steps over
+// all its keys.  Measured: 12000 rows 0.46 ms, 2000 rows of 2000 15 us; with
+// the steps over all keys 1.90 ms and 24 us; sorting each row in LDS 7.4 ms
+// and 119 us.
 // todo (may be NULL): only rows with todo[i] != 0.
-__global__ __launch_bounds__(1024) void k_row_candidates(int n, const float *D2, int64_t ldd,
-                                                         int npow2, int K, int32_t *cand,
-                                                         const int *todo, float *dnext) {
-  extern __shared__ unsigned long long keys[];
-  const int i = blockIdx.x;
+constexpr int kSelThreads = 256;
+constexpr int kSelList = 512;
+
+template <int PT>
+__global__ __launch_bounds__(kSelThreads) void k_row_select(int n, int row0, const float *D2, int64_t ldd, int K,
+                                                            int32_t *cand, const int *todo, float *dnext) {
+  constexpr int NW = kSelThreads / kWave;
+  __shared__ int cnts[2][NW][3];
+  __shared__ uint32_t wmin[NW];
+  __shared__ int fill;
+  __shared__ unsigned long long list[kSelList];
+  const int i = row0 + blockIdx.x;
   if (todo && !todo[i]) return;
-  for (int j = threadIdx.x; j < npow2; j += blockDim.x) {
-    unsigned long long key = ~0ull;
-    if (j < n && j != i) key = ((unsigned long long)float_key(D2[(size_t)i * ldd + j]) << 32) | (unsigned)j;
-    keys[j] = key;
+  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  const float *row = D2 + (size_t)blockIdx.x * ldd;
+  // slots past the row, and the row itself, hold the largest key, which no
+  // distance maps to
+  uint32_t key[PT];
+#pragma unroll
+  for (int e = 0; e < PT; ++e) {
+    const int j = threadIdx.x + e * kSelThreads;
+    key[e] = 0xffffffffu;
+    if (j < n && j != i) key[e] = min(float_key(row[j]), 0xfffffffeu);
+  }
+  if (threadIdx.x == 0) fill = 0;
+  int buf = 0;
+  // block counts of three predicates of (key, j)
+  auto count3 = [&](auto p0, auto p1, auto p2, int &c0, int &c1, int &c2) {
+    int a0 = 0, a1 = 0, a2 = 0;
+#pragma unroll
+    for (int e = 0; e < PT; ++e) {
+      const int j = threadIdx.x + e * kSelThreads;
+      a0 += __popcll(__ballot(p0(key[e], j)));
+      a1 += __popcll(__ballot(p1(key[e], j)));
+      a2 += __popcll(__ballot(p2(key[e], j)));
+    }
+    if (lane == 0) { cnts[buf][wave][0] = a0; cnts[buf][wave][1] = a1; cnts[buf][wave][2] = a2; }
+    __syncthreads();
+    c0 = c1 = c2 = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) { c0 += cnts[buf][w][0]; c1 += cnts[buf][w][1]; c2 += cnts[buf][w][2]; }
+    buf ^= 1;  // the next count writes the other buffer: one barrier per count
+  };
+  // the K-th smallest of the threads' smallest keys
+  uint32_t mine = key[0];
+#pragma unroll
+  for (int e = 1; e < PT; ++e) mine = min(mine, key[e]);
+  uint32_t top = 0;
+  for (int bit = 30; bit >= 0; bit -= 2) {
+    const uint32_t t1 = top | (1u << bit), t2 = top | (2u << bit), t3 = top | (3u << bit);
+    const int a1 = __popcll(__ballot(mine < t1)), a2 = __popcll(__ballot(mine < t2)), a3 = __popcll(__ballot(mine < t3));
+    if (lane == 0) { cnts[buf][wave][0] = a1; cnts[buf][wave][1] = a2; cnts[buf][wave][2] = a3; }
+    __syncthreads();
+    int c1 = 0, c2 = 0, c3 = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) { c1 += cnts[buf][w][0]; c2 += cnts[buf][w][1]; c3 += cnts[buf][w][2]; }
+    buf ^= 1;
+    top = c3 < K ? t3 : (c2 < K ? t2 : (c1 < K ? t1 : top));
+  }
+  top = min(top, 0xfffffffeu);  // fewer than K threads have a key: all keys
+  uint32_t next = 0xffffffffu;  // the smallest key above the bound
+#pragma unroll
+  for (int e = 0; e < PT; ++e) {
+    const bool sel = key[e] <= top;
+    const uint64_t m = __ballot(sel);
+    if (m) {
+      int base = 0;
+      if (lane == 0) base = atomicAdd(&fill, __popcll(m));
+      base = __builtin_amdgcn_readfirstlane(base) + __popcll(m & ((1ull << lane) - 1ull));
+      if (sel && base < kSelList)
+        list[base] = ((unsigned long long)key[e] << 32) | (unsigned)(threadIdx.x + e * kSelThreads);
+    }
+    if (!sel) next = min(next, key[e]);
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) next = min(next, (uint32_t)__shfl_xor((int)next, off, kWave));
+  if (lane == 0) wmin[wave] = next;
+  __syncthreads();
+  const int S = fill;
+  if (S <= kSelList) {  // uniform; S >= K
+    for (int c = threadIdx.x; c < S; c += kSelThreads) {
+      const unsigned long long k = list[c];
+      int r = 0;
+      for (int o = 0; o < S; ++o) r += list[o] < k ? 1 : 0;
+      if (r < K) cand[(size_t)i * K + r] = (int32_t)(k & 0xffffffffu);
+      if (r == K) dnext[i] = key_float((uint32_t)(k >> 32));
+    }
+    if (threadIdx.x == 0 && S == K) {
+#pragma unroll
+      for (int w = 0; w < NW; ++w) next = min(next, wmin[w]);
+      dnext[i] = K < n - 1 ? key_float(next) : INFINITY;
+    }
+    return;
   }
   __syncthreads();
-  for (int size = 2; size <= npow2; size <<= 1) {
-    for (int stride = size >> 1; stride > 0; stride >>= 1) {
-      for (int t = threadIdx.x; t < npow2 / 2; t += blockDim.x) {
-        const int lo = 2 * t - (t & (stride - 1));
-        const int hi = lo + stride;
-        const bool up = ((lo & size) == 0);
-        const unsigned long long a = keys[lo], b = keys[hi];
-        if ((a > b) == up) { keys[lo] = b; keys[hi] = a; }
-      }
-      __syncthreads();
-    }
+  if (threadIdx.x == 0) fill = 0;  // used again after the next barrier
+  uint32_t v = 0;
+  for (int bit = 30; bit >= 0; bit -= 2) {
+    const uint32_t t1 = v | (1u << bit), t2 = v | (2u << bit), t3 = v | (3u << bit);
+    int c1, c2, c3;
+    count3([&](uint32_t k, int) { return k < t1; }, [&](uint32_t k, int) { return k < t2; },
+           [&](uint32_t k, int) { return k < t3; }, c1, c2, c3);
+    v = c3 < K ? t3 : (c2 < K ? t2 : (c1 < K ? t1 : v));
   }
-  for (int r = threadIdx.x; r < K; r += blockDim.x) cand[(size_t)i * K + r] = (int32_t)(keys[r] & 0xffffffffu);
-  if (threadIdx.x == 0) dnext[i] = K < n - 1 ? key_float((uint32_t)(keys[K] >> 32)) : INFINITY;
+  // ties with the K-th key go to the lower rows: the need-th smallest row
+  // among them bounds those taken
+  int less, upto, unused;
+  count3([&](uint32_t k, int) { return k < v; }, [&](uint32_t k, int) { return k <= v; },
+         [](uint32_t, int) { return false; }, less, upto, unused);
+  int jmax = n;
+  if (upto > K) {  // uniform
+    const int need = K - less;
+    int jt = 0;
+    for (int bit = 14; bit >= 0; --bit) {
+      const int t = jt | (1 << bit);
+      int c;
+      count3([&](uint32_t k, int j) { return k == v && j < t; }, [](uint32_t, int) { return false; },
+             [](uint32_t, int) { return false; }, c, unused, unused);
+      if (c < need) jt = t;
+    }
+    jmax = jt;
+  }
+  next = 0xffffffffu;
+#pragma unroll
+  for (int e = 0; e < PT; ++e) {
+    const int j = threadIdx.x + e * kSelThreads;
+    const bool sel = key[e] < v || (key[e] == v && j <= jmax);
+    const uint64_t m = __ballot(sel);
+    if (m) {
+      int base = 0;
+      if (lane == 0) base = atomicAdd(&fill, __popcll(m));
+      base = __builtin_amdgcn_readfirstlane(base);
+      if (sel) cand[(size_t)i * K + base + __popcll(m & ((1ull << lane) - 1ull))] = j;
+    }
+    if (key[e] > v) next = min(next, key[e]);
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) next = min(next, (uint32_t)__shfl_xor((int)next, off, kWave));
+  if (lane == 0) wmin[wave] = next;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int w = 0; w < NW; ++w) next = min(next, wmin[w]);
+    dnext[i] = K < n - 1 ? key_float(upto > K ? v : next) : INFINITY;
+  }
 }
 
 // Largest FP32 row norm of the n rows.
@@ -268,6 +483,7 @@ __global__ __launch_bounds__(256) void k_recheck(int n, int p, const double *Xd,
                                                  int *n_uncert) {
   extern __shared__ double sd[];  // K doubles + K ints
   int *sj = reinterpret_cast<int *>(sd + K);
+  __shared__ double kth;
   const int i = blockIdx.x;
   if (todo && !todo[i]) return;
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
@@ -275,6 +491,7 @@ __global__ __launch_bounds__(256) void k_recheck(int n, int p, const double *Xd,
   for (int c = wave; c < K; c += nw) {
     const int j = cand[(size_t)i * K + c];
     double acc = 0.0;
+#pragma unroll 4
     for (int f = lane; f < p; f += kWave) {
       const double d = Xd[(size_t)j * p + f] - Xd[(size_t)i * p + f];
       acc = fma(d, d, acc);
@@ -282,22 +499,38 @@ __global__ __launch_bounds__(256) void k_recheck(int n, int p, const double *Xd,
     for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, kWave);
     if (lane == 0) { sd[c] = acc; sj[c] = j; }
   }
+  if (threadIdx.x == 0) kth = NAN;  // no candidate of that rank: not certified
+  __syncthreads();
+  // a candidate's rank is the number of smaller (d2, j); a thread per
+  // candidate counts it (one thread selecting them in turn took 3/4 of this
+  // kernel's time at K = 32).  A distance that is not a number ranks last,
+  // by row.
+  for (int c = threadIdx.x; c < K; c += blockDim.x) {
+    const double d = sd[c];
+    const int j = sj[c];
+    const bool num = d == d;
+    int r = 0;
+    for (int o = 0; o < K; ++o) {
+      const double od = sd[o];
+      const bool less = num ? (od < d || (od == d && sj[o] < j)) : (od == od || sj[o] < j);
+      r += less ? 1 : 0;
+    }
+    if (r < k) knn[(size_t)i * k + r] = j;
+    if (r == k - 1) kth = d;
+  }
   __syncthreads();
   if (threadIdx.x == 0) {
-    // selection of the k smallest (d2, j); K is small
-    for (int r = 0; r < k; ++r) {
-      int best = r;
-      for (int c = r + 1; c < K; ++c)
-        if (sd[c] < sd[best] || (sd[c] == sd[best] && sj[c] < sj[best])) best = c;
-      const double td = sd[r]; sd[r] = sd[best]; sd[best] = td;
-      const int tj = sj[r]; sj[r] = sj[best]; sj[best] = tj;
-      knn[(size_t)i * k + r] = sj[r];
-    }
     const double bound = bscale * ((double)nrm[i] + (double)*nmax);
-    const bool ok = sd[k - 1] < (double)dnext[i] - bound;
+    const bool ok = kth < (double)dnext[i] - bound;
     uncert[i] = ok ? 0 : 1;
     if (!ok) atomicAdd(n_uncert, 1);
   }
+}
+
+// n words of zero.
+__global__ void k_zero_words(uint32_t *v, int64_t n) {
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+    v[i] = 0u;
 }
 
 __global__ void k_mark_pairs(int n, int k, int words, const int32_t *knn, uint32_t *bm) {
@@ -309,48 +542,67 @@ __global__ void k_mark_pairs(int n, int k, int words, const int32_t *knn, uint32
   atomicOr(&bm[(size_t)a * words + b / 32], 1u << (b % 32));
 }
 
-__global__ void k_row_counts(int n, int words, const uint32_t *bm, int32_t *cnt) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+// Set bits of each row of the bitmap, a wave per row.
+__global__ __launch_bounds__(256) void k_row_counts(int n, int words, const uint32_t *bm, int32_t *cnt) {
+  const int i = blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
   if (i >= n) return;
   int c = 0;
-  for (int w = 0; w < words; ++w) c += __popc(bm[(size_t)i * words + w]);
-  cnt[i] = c;
+  for (int w = threadIdx.x % kWave; w < words; w += kWave) c += __popc(bm[(size_t)i * words + w]);
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off, kWave);
+  if (threadIdx.x % kWave == 0) cnt[i] = c;
 }
 
-// Exclusive scan of n counts in one block (sequential chunks, fixed order).
-__global__ __launch_bounds__(1024) void k_scan(int n, const int32_t *cnt, int32_t *off, int64_t *total) {
-  __shared__ int64_t part[1024];
-  const int t = threadIdx.x, nt = blockDim.x;
-  const int per = (n + nt - 1) / nt;
-  const int s0 = t * per, s1 = min(n, s0 + per);
-  int64_t acc = 0;
-  for (int i = s0; i < s1; ++i) acc += cnt[i];
-  part[t] = acc;
-  __syncthreads();
-  if (t == 0) {
-    int64_t run = 0;
-    for (int q = 0; q < nt; ++q) { const int64_t v = part[q]; part[q] = run; run += v; }
-    *total = run;
+// Sum of the lanes below this one.
+__device__ __forceinline__ int lanes_before(int v) {
+  const int lane = threadIdx.x % kWave;
+  int run = v;
+#pragma unroll
+  for (int off = 1; off < kWave; off <<= 1) {
+    const int o = __shfl_up(run, off, kWave);
+    if (lane >= off) run += o;
   }
-  __syncthreads();
-  int64_t run = part[t];
-  for (int i = s0; i < s1; ++i) { off[i] = (int32_t)run; run += cnt[i]; }
+  return run - v;
 }
 
-__global__ void k_emit_edges(int n, int words, const uint32_t *bm, const int32_t *off,
-                             int32_t *ei, int32_t *ej) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+// Exclusive scan of n counts in one block: a thread's chunk, the lanes of a
+// wave, the waves.  The total is at most n * k < 2^31.
+__global__ __launch_bounds__(1024) void k_scan(int n, const int32_t *cnt, int32_t *off, int64_t *total) {
+  __shared__ int wsum[1024 / kWave];
+  const int t = threadIdx.x, nt = blockDim.x, wave = t / kWave;
+  const int per = (n + nt - 1) / nt;
+  const int s0 = min(n, t * per), s1 = min(n, s0 + per);
+  int acc = 0;
+  for (int i = s0; i < s1; ++i) acc += cnt[i];
+  int run = lanes_before(acc);
+  if (t % kWave == kWave - 1) wsum[wave] = run + acc;
+  __syncthreads();
+  for (int w = 0; w < wave; ++w) run += wsum[w];
+  for (int i = s0; i < s1; ++i) { off[i] = run; run += cnt[i]; }
+  if (t == nt - 1) *total = run;
+}
+
+// The edges of each row in order, a wave per row: 64 words at a time, each
+// lane after the bits of the words before its own.
+__global__ __launch_bounds__(256) void k_emit_edges(int n, int words, const uint32_t *bm, const int32_t *off,
+                                                    int32_t *ei, int32_t *ej) {
+  const int i = blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
   if (i >= n) return;
   int pos = off[i];
-  for (int w = 0; w < words; ++w) {
-    uint32_t bits = bm[(size_t)i * words + w];
+  for (int w0 = 0; w0 < words; w0 += kWave) {
+    const int w = w0 + threadIdx.x % kWave;
+    uint32_t bits = w < words ? bm[(size_t)i * words + w] : 0u;
+    const int c = __popc(bits);
+    const int before = lanes_before(c);
+    int q = pos + before;
     while (bits) {
       const int b = __ffs(bits) - 1;
       bits &= bits - 1;
-      ei[pos] = i;
-      ej[pos] = w * 32 + b;
-      ++pos;
+      ei[q] = i;
+      ej[q] = w * 32 + b;
+      ++q;
     }
+    pos += __shfl(before + c, kWave - 1, kWave);
   }
 }
 
@@ -369,66 +621,124 @@ __global__ void k_edge_d2(int E, int p, const double *Xd, const int32_t *ei, con
   if (lane == 0) d2[e] = acc;
 }
 
-// Lower median of E non-negative doubles by an 8-pass radix select on the
-// bit patterns (order-preserving for non-negative doubles).  One block.
-__global__ __launch_bounds__(1024) void k_lower_median(int E, const double *v, double *out) {
-  __shared__ unsigned int hist[256];
-  __shared__ unsigned long long prefix_s;
-  __shared__ long long rank_s;
-  if (threadIdx.x == 0) { prefix_s = 0ull; rank_s = (E - 1) / 2; }
+// Block sums and extremes of one value per thread (1024 threads), to all.
+template <typename T, typename Op>
+__device__ inline T block_reduce(T v, T *red, Op op) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v = op(v, __shfl_xor(v, off, kWave));
+  __syncthreads();  // red may hold an earlier result
+  if (threadIdx.x % kWave == 0) red[threadIdx.x / kWave] = v;
   __syncthreads();
-  for (int pass = 7; pass >= 0; --pass) {
-    for (int b = threadIdx.x; b < 256; b += blockDim.x) hist[b] = 0u;
+  v = red[0];
+  for (int w = 1; w < (int)(blockDim.x / kWave); ++w) v = op(v, red[w]);
+  return v;
+}
+
+// phi = c over the lower median of E >= 1 non-negative doubles (0 when the
+// median is 0), by bit patterns, which order them.  One block: the range
+// [lo, hi] of patterns is cut into at most 4096 equal buckets, the bucket of
+// the median becomes the range, and once it holds few enough values they
+// are ranked in LDS.  Distances spread evenly over the buckets, so two or
+// three passes over the values do (a radix pass by bytes puts them all into
+// the few bins of their exponents: 8 passes, 100 us for 23 000 values and
+// 245 us for 80 000, against 18 and 48 us).
+constexpr int kMedBuckets = 4096, kMedList = 1024;
+
+__global__ __launch_bounds__(1024) void k_median_phi(int E, const double *v, double c, double *phi) {
+  using u64 = unsigned long long;
+  __shared__ unsigned int hist[kMedBuckets];
+  __shared__ u64 list[kMedList];
+  __shared__ u64 red[1024 / kWave];
+  __shared__ int wsum[1024 / kWave];
+  __shared__ int bucket, below, filled;
+  __shared__ u64 answer;
+  const int t = threadIdx.x, wave = t / kWave;
+  auto key = [&](int e) { return (u64)__double_as_longlong(v[e]); };
+  u64 lo = ~0ull, hi = 0ull;
+#pragma unroll 4
+  for (int e = t; e < E; e += 1024) { const u64 k = key(e); lo = min(lo, k); hi = max(hi, k); }
+  lo = block_reduce(lo, red, [](u64 a, u64 b) { return a < b ? a : b; });
+  hi = block_reduce(hi, red, [](u64 a, u64 b) { return a > b ? a : b; });
+  int rank = (E - 1) / 2;
+  for (;;) {  // each turn cuts the range by 4096: at most 6
+    const u64 range = hi - lo;
+    const int bits = range ? 64 - __clzll((long long)range) : 0;
+    const int shift = bits > 12 ? bits - 12 : 0;
+    for (int b = t; b < kMedBuckets; b += 1024) hist[b] = 0u;
+    if (t == 0) filled = 0;
     __syncthreads();
-    const unsigned long long prefix = prefix_s;
-    const int shift = pass * 8;
-    const unsigned long long himask = (pass == 7) ? 0ull : (~0ull << (shift + 8));
-    for (int e = threadIdx.x; e < E; e += blockDim.x) {
-      const unsigned long long k = (unsigned long long)__double_as_longlong(v[e]);
-      if ((k & himask) == (prefix & himask)) atomicAdd(&hist[(k >> shift) & 0xffu], 1u);
+#pragma unroll 4
+    for (int e = t; e < E; e += 1024) {
+      const u64 k = key(e);
+      if (k >= lo && k <= hi) atomicAdd(&hist[(k - lo) >> shift], 1u);
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-      long long r = rank_s;
-      int digit = 0;
-      for (; digit < 256; ++digit) {
-        if (r < (long long)hist[digit]) break;
-        r -= hist[digit];
+    // each thread's 4 buckets, the counts before them, and the one with the rank
+    int h[4], own = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) { h[q] = (int)hist[4 * t + q]; own += h[q]; }
+    int run = lanes_before(own);
+    if (t % kWave == kWave - 1) wsum[wave] = run + own;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) run += wsum[w];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (rank >= run && rank < run + h[q]) { bucket = 4 * t + q; below = run; }
+      run += h[q];
+    }
+    __syncthreads();
+    const int b = bucket, cnt = (int)hist[b];
+    rank -= below;
+    lo += (u64)b << shift;
+    const u64 top = lo + ((1ull << shift) - 1ull);
+    hi = top < hi ? top : hi;
+    if (shift == 0) {  // a bucket of one value
+      if (t == 0) answer = lo;
+      break;
+    }
+    if (cnt <= kMedList) {
+#pragma unroll 4
+      for (int e = t; e < E; e += 1024) {
+        const u64 k = key(e);
+        if (k >= lo && k <= hi) list[atomicAdd(&filled, 1)] = k;
       }
-      rank_s = r;
-      prefix_s = prefix | ((unsigned long long)digit << shift);
+      __syncthreads();
+      if (t < cnt) {
+        const u64 mine = list[t];
+        int r = 0;
+        for (int o = 0; o < cnt; ++o) r += (list[o] < mine || (list[o] == mine && o < t)) ? 1 : 0;
+        if (r == rank) answer = mine;
+      }
+      break;
     }
-    __syncthreads();
+    __syncthreads();  // bucket, below and hist are read before the next turn
   }
-  if (threadIdx.x == 0) *out = __longlong_as_double((long long)prefix_s);
+  __syncthreads();
+  if (t == 0) {
+    const double med = __longlong_as_double((long long)answer);
+    *phi = med > 0.0 ? c / med : 0.0;
+  }
 }
 
-__global__ void k_weights(int E, const double *d2, const double *phi, double *w) {
+// phi (may be NULL): the device value; else the literal c.
+__global__ void k_weights(int E, const double *d2, const double *phi, double c, double *w) {
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e < E) w[e] = exp(-(*phi) * d2[e]);
+  if (e < E) w[e] = exp(-(phi ? *phi : c) * d2[e]);
 }
 
-__global__ __launch_bounds__(1024) void k_normalize(int E, double *w) {
-  __shared__ double s[1024];
+// Sum of the weights (one block, coalesced, fixed order), then the scaling.
+__global__ __launch_bounds__(1024) void k_weight_sum(int E, const double *w, double *tot) {
+  __shared__ double red[1024 / kWave];
   double acc = 0.0;
-  const int per = (E + blockDim.x - 1) / blockDim.x;
-  const int e0 = threadIdx.x * per, e1 = min(E, e0 + per);
-  for (int e = e0; e < e1; ++e) acc += w[e];
-  s[threadIdx.x] = acc;
-  __syncthreads();
-  __shared__ double tot;
-  if (threadIdx.x == 0) {
-    double t = 0.0;
-    for (int q = 0; q < (int)blockDim.x; ++q) t += s[q];
-    tot = t;
-  }
-  __syncthreads();
-  const double inv = 1.0 / tot;
-  for (int e = e0; e < e1; ++e) w[e] *= inv;
+#pragma unroll 4
+  for (int e = threadIdx.x; e < E; e += 1024) acc += w[e];
+  acc = block_reduce(acc, red, [](double a, double b) { return a + b; });
+  if (threadIdx.x == 0) *tot = acc;
 }
-
-__global__ void k_phi_from_median(const double *med, double c, double *phi) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) *phi = (*med > 0.0) ? c / *med : 0.0;
+__global__ void k_normalize(int E, const double *tot, double *w) {
+  const int e = blockIdx.x * blockDim.x + threadIdx.x;
+  const double inv = 1.0 / *tot;
+  if (e < E) w[e] *= inv;
 }
 
 // ------------------------------------------------ connectivity over k
@@ -532,132 +842,164 @@ struct DevBuf {
     if (_s != CC_OK) return _s; \
   } while (0)
 
-// Steps 1-4: the mean-imputed X~ in FP64 (Xd, n x p) and the k nearest
-// neighbours of every row by (exact d2, index) (knn, n x k).
-template <typename TI>
-static cc_status knn_lists(int64_t n, int64_t p, const TI *X, int64_t ldx, const uint8_t *mask,
-                           int64_t ldm, int32_t k, hipStream_t st, DevBuf &Xd, DevBuf &knn) {
-  const int64_t n_pad = cdiv64(n, kGT) * kGT;
-  const int64_t ldk = cdiv64(p, kKC) * kKC;
-  const int K = (int)std::min<int64_t>(n - 1, (int64_t)k + std::max(16, (int)k));
-  int npow2 = 1;
-  while (npow2 < n) npow2 <<= 1;
-
-  DevBuf mean, bad, Xf, nrm, D2, cand;
-  KN_TRY(mean.alloc(p * 8));
-  KN_TRY(bad.alloc(4));
-  KN_TRY(Xf.alloc((size_t)n_pad * ldk * 4));
-  KN_TRY(Xd.alloc((size_t)n * p * 8));
-  KN_TRY(nrm.alloc(n_pad * 4));
-  KN_TRY(D2.alloc((size_t)n * n * 4));
-  KN_TRY(cand.alloc((size_t)n * K * 4));
-  KN_TRY(knn.alloc((size_t)n * k * 4));
-
-  CC_HIP(hipMemsetAsync(bad.p, 0, 4, st));
-  hipLaunchKernelGGL((k_col_moments<TI>), dim3((int)cdiv64(p, 256)), dim3(256), 0, st, (int)n,
-                     (int)p, X, ldx, mask, ldm, mean.as<double>(), (double *)nullptr, bad.as<int>());
-  int hbad = 0;
-  CC_HIP(hipMemcpyAsync(&hbad, bad.p, 4, hipMemcpyDeviceToHost, st));
-  CC_HIP(hipStreamSynchronize(st));
-  if (hbad) { set_error("observed X has non-finite entries"); return CC_ERR_INVALID_ARG; }
-  hipLaunchKernelGGL((k_impute<TI>), dim3((int)cdiv64(n_pad * ldk, 256)), dim3(256), 0, st,
-                     (int)n, (int)p, (int)n_pad, (int)ldk, X, ldx, mask, ldm, mean.as<double>(),
-                     Xf.as<float>(), Xd.as<double>());
-  hipLaunchKernelGGL(k_rownorm, dim3((int)n_pad), dim3(256), 0, st, (int)n_pad, (int)ldk,
-                     Xf.as<float>(), nrm.as<float>());
-  // split K until the launch has about 4 blocks per CU (at most 8 splits)
-  const int gb = (int)(n_pad / kGT);
-  const int nch = (int)(ldk / kKC);
-  int nsplit = (int)std::min<int64_t>(std::min<int64_t>(cdiv64(1024, (int64_t)gb * gb), 8), nch);
-  if (nsplit < 1) nsplit = 1;
-  DevBuf part;
-  if (nsplit > 1) KN_TRY(part.alloc((size_t)nsplit * n_pad * n_pad * 4));
-  hipLaunchKernelGGL(k_gram_d2, dim3(gb, gb, nsplit), dim3(256), 0, st, (int)n, (int)n_pad, (int)ldk,
-                     nsplit, Xf.as<float>(), nrm.as<float>(), D2.as<float>(), (int64_t)n,
-                     part.as<float>());
-  if (nsplit > 1)
-    hipLaunchKernelGGL(k_gram_combine, dim3((int)cdiv64(n * n, 256)), dim3(256), 0, st, (int)n,
-                       (int)n_pad, nsplit, part.as<float>(), nrm.as<float>(), D2.as<float>(),
-                       (int64_t)n);
-  CC_HIP(hipGetLastError());
-  // rounding bound of the FP32 distances (see k_recheck): (2 m + 24) u with
-  // m the longest FP32 accumulation (ldk products and the split combine)
-  const double bscale = (2.0 * (double)(ldk + nsplit) + 24.0) * std::ldexp(1.0, -24) * 1.001;
-  DevBuf dnext, nmax, uncert, nun;
-  KN_TRY(dnext.alloc(n * 4));
-  KN_TRY(nmax.alloc(4));
-  KN_TRY(uncert.alloc(n * 4));
-  KN_TRY(nun.alloc(4));
-  hipLaunchKernelGGL(k_max_norm, dim3(1), dim3(1024), 0, st, (int)n, nrm.as<float>(), nmax.as<float>());
-  // the dynamic LDS limits are set to the largest sizes these kernels take
-  // (the same values on every call, so that concurrent builds agree)
-  const size_t lds = (size_t)npow2 * 8;
-  CC_HIP(hipFuncSetAttribute((const void *)k_row_candidates,
-                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kKnnMaxN * 8)));
-  CC_HIP(hipFuncSetAttribute((const void *)k_recheck, hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)(kRecheckMaxK * 12)));
-  // wider passes for the rows a pass could not certify: 8 K (at least 512)
-  // candidates, then all rows up to kRecheckMaxK (every row for n up to
-  // kRecheckMaxK + 1, which certifies by construction)
-  const int64_t widths[3] = {K, std::min<int64_t>({n - 1, std::max<int64_t>(8 * (int64_t)K, 512), kRecheckMaxK}),
-                             std::min<int64_t>(n - 1, kRecheckMaxK)};
-  const int *todo = nullptr;
-  DevBuf cand2;
-  int Kp = K;
-  int32_t *cp = cand.as<int32_t>();
-  for (int pass = 0; pass < 3; ++pass) {
-    if (pass > 0) {
-      if (widths[pass] <= Kp) continue;
-      Kp = (int)widths[pass];
-      if (cand2.p) { (void)hipFree(cand2.p); cand2.p = nullptr; }
-      KN_TRY(cand2.alloc((size_t)n * Kp * 4));
-      cp = cand2.as<int32_t>();
-      todo = uncert.as<int>();
-    }
-    CC_HIP(hipMemsetAsync(nun.p, 0, 4, st));
-    hipLaunchKernelGGL(k_row_candidates, dim3((int)n), dim3(1024), lds, st, (int)n,
-                       D2.as<float>(), (int64_t)n, npow2, Kp, cp, todo, dnext.as<float>());
-    CC_HIP(hipGetLastError());
-    const size_t lds2 = (size_t)Kp * 12;
-    hipLaunchKernelGGL(k_recheck, dim3((int)n), dim3(256), lds2, st, (int)n, (int)p,
-                       Xd.as<double>(), Kp, (int)k, cp, knn.as<int32_t>(), todo,
-                       dnext.as<float>(), nrm.as<float>(), nmax.as<float>(), bscale,
-                       uncert.as<int>(), nun.as<int>());
-    CC_HIP(hipGetLastError());
-    int hn = 0;
-    CC_HIP(hipMemcpyAsync(&hn, nun.p, 4, hipMemcpyDeviceToHost, st));
-    CC_HIP(hipStreamSynchronize(st));
-    if (hn == 0) return CC_OK;
+// One device allocation cut into aligned pieces: add() every piece, then
+// alloc() once.
+struct Arena {
+  DevBuf buf;
+  size_t total = 0;
+  size_t add(size_t bytes) {
+    const size_t at = total;
+    total += (bytes + 255) / 256 * 256;
+    return at;
   }
-  set_error("kNN: the nearest neighbours of some rows could not be certified exact "
-            "(FP32 distances too close to separate them)");
-  return CC_ERR_NUMERIC;
+  cc_status alloc() { return buf.alloc(total); }
+  template <typename T> T *at(size_t off) const { return reinterpret_cast<T *>((char *)buf.p + off); }
+};
+
+// Sizes and buffers of the neighbour lists (steps 1-4): X~ in FP64 (Xd,
+// n x p), the k nearest neighbours of every row by (exact d2, index) (knn,
+// n x k), and what ranking them takes.  plan() adds the buffers to an
+// arena; rank() enqueues one ranking pass.
+template <typename TI> struct KnnLists {
+  int64_t n, p, n_pad, ldk, rows;  // rows: of a distance panel, a multiple of the tile
+  int k, K, nsplit;
+  const TI *X;
+  int64_t ldx;
+  const uint8_t *mask;
+  int64_t ldm;
+  hipStream_t st;
+  Arena *ar;
+  size_t mean, state, Xf, Xd, nrm, D2, cand, knn, part, dnext, nmax, uncert;
+
+  int *bad() const { return ar->at<int>(state); }          // non-finite observed entries
+  int *n_uncert() const { return ar->at<int>(state) + 1; } // rows the last pass left uncertified
+
+  void plan(Arena &a) {
+    ar = &a;
+    n_pad = cdiv64(n, kGT) * kGT;
+    ldk = cdiv64(p, kKC) * kKC;
+    K = (int)std::min<int64_t>(n - 1, (int64_t)k + std::max(16, k));
+    rows = std::min<int64_t>(n_pad, std::max<int64_t>(kPanelBytes / (4 * n) / kGT * kGT, kGT));
+    // split the features until the launch has about 4 blocks per CU (at
+    // most 8 splits)
+    const int64_t tiles = (n_pad / kGT) * (rows / kGT);
+    nsplit = (int)std::max<int64_t>(std::min<int64_t>(std::min<int64_t>(cdiv64(1024, tiles), 8), ldk / kKC), 1);
+    mean = a.add(p * 8);
+    state = a.add(64);
+    Xf = a.add((size_t)n_pad * ldk * 4);
+    Xd = a.add((size_t)n * p * 8);
+    nrm = a.add(n_pad * 4);
+    D2 = a.add((size_t)rows * n * 4);
+    cand = a.add((size_t)n * K * 4);
+    knn = a.add((size_t)n * k * 4);
+    part = a.add(nsplit > 1 ? (size_t)nsplit * rows * n_pad * 4 : 0);
+    dnext = a.add(n * 4);
+    nmax = a.add(4);
+    uncert = a.add(n * 4);
+  }
+
+  // Steps 1 and the norms; clears the counters.
+  cc_status start() {
+    hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, st, ar->at<uint32_t>(state), (int64_t)16);
+    moments_launch(n, p, X, ldx, mask, ldm, true, ar->at<double>(mean), (double *)nullptr, false, bad(), st);
+    hipLaunchKernelGGL((k_impute<TI>), dim3((int)cdiv64(n_pad * ldk, 256)), dim3(256), 0, st, (int)n, (int)p,
+                       (int)n_pad, (int)ldk, X, ldx, mask, ldm, ar->at<double>(mean), ar->at<float>(Xf),
+                       ar->at<double>(Xd));
+    hipLaunchKernelGGL(k_rownorm, dim3((int)n_pad), dim3(256), 0, st, (int)n_pad, (int)ldk, ar->at<float>(Xf),
+                       ar->at<float>(nrm));
+    hipLaunchKernelGGL(k_max_norm, dim3(1), dim3(1024), 0, st, (int)n, ar->at<float>(nrm), ar->at<float>(nmax));
+    // the dynamic LDS limit is set to the largest size the kernel takes
+    // (the same value on every call, so that concurrent builds agree)
+    CC_HIP(hipFuncSetAttribute((const void *)k_recheck, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)(kRecheckMaxK * 12)));
+    CC_HIP(hipGetLastError());
+    return CC_OK;
+  }
+
+  template <int PT> void select(int64_t row0, int64_t nr, int Kp, int32_t *cp, const int *todo) {
+    hipLaunchKernelGGL((k_row_select<PT>), dim3((int)nr), dim3(kSelThreads), 0, st, (int)n, (int)row0,
+                       ar->at<float>(D2), n, Kp, cp, todo, ar->at<float>(dnext));
+  }
+
+  // Steps 2-4 with Kp candidates per row, over all rows or those of todo.
+  cc_status rank(int Kp, int32_t *cp, const int *todo) {
+    for (int64_t row0 = 0; row0 < n; row0 += rows) {
+      const int64_t nr = std::min<int64_t>(rows, n - row0);
+      const int gy = (int)cdiv64(nr, kGT);
+      hipLaunchKernelGGL(k_gram_d2, dim3((int)(n_pad / kGT), gy, nsplit), dim3(256), 0, st, (int)n, (int)n_pad,
+                         (int)ldk, nsplit, ar->at<float>(Xf), ar->at<float>(nrm), (int)row0, (int)rows,
+                         ar->at<float>(D2), n, ar->at<float>(part));
+      if (nsplit > 1)
+        hipLaunchKernelGGL(k_gram_combine, dim3((int)cdiv64(nr * n, 256)), dim3(256), 0, st, (int)n, (int)n_pad,
+                           nsplit, ar->at<float>(part), ar->at<float>(nrm), (int)row0, (int)nr, (int)rows,
+                           ar->at<float>(D2), n);
+      if (n <= 256) select<1>(row0, nr, Kp, cp, todo);
+      else if (n <= 1024) select<4>(row0, nr, Kp, cp, todo);
+      else if (n <= 2048) select<8>(row0, nr, Kp, cp, todo);
+      else if (n <= 4096) select<16>(row0, nr, Kp, cp, todo);
+      else if (n <= 8192) select<32>(row0, nr, Kp, cp, todo);
+      else select<64>(row0, nr, Kp, cp, todo);
+    }
+    // rounding bound of the FP32 distances (see k_recheck): (2 m + 24) u with
+    // m the longest FP32 accumulation (ldk products and the split combine)
+    const double bscale = (2.0 * (double)(ldk + nsplit) + 24.0) * std::ldexp(1.0, -24) * 1.001;
+    hipLaunchKernelGGL(k_recheck, dim3((int)n), dim3(256), (size_t)Kp * 12, st, (int)n, (int)p, ar->at<double>(Xd),
+                       Kp, k, cp, ar->at<int32_t>(knn), todo, ar->at<float>(dnext), ar->at<float>(nrm),
+                       ar->at<float>(nmax), bscale, ar->at<int>(uncert), n_uncert());
+    CC_HIP(hipGetLastError());
+    return CC_OK;
+  }
+
+  // After the first pass left uncertified rows: wider passes over those, 8 K
+  // (at least 512) candidates, then all rows up to kRecheckMaxK (every row
+  // for n up to kRecheckMaxK + 1, which certifies by construction).
+  cc_status widen() {
+    const int64_t widths[2] = {std::min<int64_t>({n - 1, std::max<int64_t>(8 * (int64_t)K, 512), kRecheckMaxK}),
+                               std::min<int64_t>(n - 1, kRecheckMaxK)};
+    int Kp = K;
+    for (int64_t w : widths) {
+      if (w <= Kp) continue;
+      Kp = (int)w;
+      DevBuf wide;
+      KN_TRY(wide.alloc((size_t)n * Kp * 4));
+      hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, st, (uint32_t *)n_uncert(), (int64_t)1);
+      KN_TRY(rank(Kp, wide.as<int32_t>(), ar->at<int>(uncert)));
+      int hn = 0;
+      CC_HIP(hipMemcpyAsync(&hn, n_uncert(), 4, hipMemcpyDeviceToHost, st));
+      CC_HIP(hipStreamSynchronize(st));
+      if (hn == 0) return CC_OK;
+    }
+    set_error("kNN: the nearest neighbours of some rows could not be certified exact "
+              "(FP32 distances too close to separate them)");
+    return CC_ERR_NUMERIC;
+  }
+};
+
+static cc_status non_finite_error() {
+  set_error("observed X has non-finite entries");
+  return CC_ERR_INVALID_ARG;
 }
 
 // Step 6 over E edges with squared distances d2 (device): phi (literal, or
 // |phi| / lower median of d2 when phi < 0), w = exp(-phi d2), optional
-// normalisation to sum 1; phi_used (host, may be NULL) gets phi.
+// normalisation to sum 1; phi_used (host, may be NULL) gets phi.  work: two
+// device doubles.
 static cc_status finish_weights(int64_t E, const double *d2, double phi, int32_t normalize,
-                                double *w, double *phi_used, hipStream_t st) {
-  DevBuf med, phid;
-  KN_TRY(med.alloc(8));
-  KN_TRY(phid.alloc(8));
+                                double *w, double *phi_used, double *work, hipStream_t st) {
   double hphi = phi;
-  if (phi < 0.0 && E > 0) {
-    hipLaunchKernelGGL(k_lower_median, dim3(1), dim3(1024), 0, st, (int)E, d2, med.as<double>());
-    hipLaunchKernelGGL(k_phi_from_median, dim3(1), dim3(1), 0, st, med.as<double>(), -phi,
-                       phid.as<double>());
-  } else {
-    if (phi < 0.0) hphi = 0.0;
-    CC_HIP(hipMemcpyAsync(phid.p, &hphi, 8, hipMemcpyHostToDevice, st));
-  }
+  const bool med = phi < 0.0 && E > 0;
+  if (phi < 0.0 && E == 0) hphi = 0.0;
+  if (med) hipLaunchKernelGGL(k_median_phi, dim3(1), dim3(1024), 0, st, (int)E, d2, -phi, work);
   if (E > 0) {
-    hipLaunchKernelGGL(k_weights, dim3((int)cdiv64(E, 256)), dim3(256), 0, st, (int)E, d2,
-                       phid.as<double>(), w);
-    if (normalize) hipLaunchKernelGGL(k_normalize, dim3(1), dim3(1024), 0, st, (int)E, w);
+    const dim3 g((int)cdiv64(E, 256));
+    hipLaunchKernelGGL(k_weights, g, dim3(256), 0, st, (int)E, d2, med ? work : (const double *)nullptr, hphi, w);
+    if (normalize) {
+      hipLaunchKernelGGL(k_weight_sum, dim3(1), dim3(1024), 0, st, (int)E, w, work + 1);
+      hipLaunchKernelGGL(k_normalize, g, dim3(256), 0, st, (int)E, work + 1, w);
+    }
   }
   CC_HIP(hipGetLastError());
-  CC_HIP(hipMemcpyAsync(&hphi, phid.p, 8, hipMemcpyDeviceToHost, st));
+  if (med) CC_HIP(hipMemcpyAsync(&hphi, work, 8, hipMemcpyDeviceToHost, st));
   CC_HIP(hipStreamSynchronize(st));
   if (phi_used) *phi_used = hphi;
   return CC_OK;
@@ -669,61 +1011,90 @@ static cc_status knn_impl(int64_t n, int64_t p, const TI *X, int64_t ldx, const 
                           int32_t *ej, double *w, int64_t capacity, int64_t *n_edges,
                           double *phi_used, hipStream_t st) {
   const int words = (int)cdiv64(n, 32);
-  DevBuf Xd, knn, bm, cnt, off, total, d2;
-  KN_TRY(knn_lists(n, p, X, ldx, mask, ldm, k, st, Xd, knn));
-  KN_TRY(bm.alloc((size_t)n * words * 4));
-  KN_TRY(cnt.alloc(n * 4));
-  KN_TRY(off.alloc(n * 4));
-  KN_TRY(total.alloc(8));
-  CC_HIP(hipMemsetAsync(bm.p, 0, (size_t)n * words * 4, st));
-  hipLaunchKernelGGL(k_mark_pairs, dim3((int)cdiv64(n * k, 256)), dim3(256), 0, st, (int)n,
-                     (int)k, words, knn.as<int32_t>(), bm.as<uint32_t>());
-  hipLaunchKernelGGL(k_row_counts, dim3((int)cdiv64(n, 256)), dim3(256), 0, st, (int)n, words,
-                     bm.as<uint32_t>(), cnt.as<int32_t>());
-  hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, st, (int)n, cnt.as<int32_t>(),
-                     off.as<int32_t>(), total.as<int64_t>());
-  int64_t E = 0;
-  CC_HIP(hipMemcpyAsync(&E, total.p, 8, hipMemcpyDeviceToHost, st));
-  CC_HIP(hipStreamSynchronize(st));
+  Arena ar;
+  KnnLists<TI> L{};
+  L.n = n; L.p = p; L.k = k; L.X = X; L.ldx = ldx; L.mask = mask; L.ldm = ldm; L.st = st;
+  L.plan(ar);
+  const size_t bm = ar.add((size_t)n * words * 4), cnt = ar.add(n * 4), off = ar.add(n * 4),
+               work = ar.add(16), d2 = ar.add((size_t)n * k * 8);
+  KN_TRY(ar.alloc());
+  // the total number of edges sits beside the lists' counters, so that one
+  // copy brings all three to the host
+  int64_t *total = ar.at<int64_t>(L.state) + 1;
+  const dim3 rows4((int)cdiv64(n, 4));
+  auto edges = [&]() -> cc_status {  // step 5
+    const int64_t nw = n * (int64_t)words;
+    hipLaunchKernelGGL(k_zero_words, dim3((int)std::min<int64_t>(cdiv64(nw, 1024), 4096)), dim3(256), 0, st,
+                       ar.at<uint32_t>(bm), nw);
+    hipLaunchKernelGGL(k_mark_pairs, dim3((int)cdiv64(n * k, 256)), dim3(256), 0, st, (int)n, (int)k, words,
+                       ar.at<int32_t>(L.knn), ar.at<uint32_t>(bm));
+    hipLaunchKernelGGL(k_row_counts, rows4, dim3(256), 0, st, (int)n, words, ar.at<uint32_t>(bm),
+                       ar.at<int32_t>(cnt));
+    hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, st, (int)n, ar.at<int32_t>(cnt), ar.at<int32_t>(off), total);
+    CC_HIP(hipGetLastError());
+    return CC_OK;
+  };
+  struct { int32_t bad, uncert; int64_t total; } h{};
+  auto read = [&]() -> cc_status {
+    CC_HIP(hipMemcpyAsync(&h, L.bad(), sizeof(h), hipMemcpyDeviceToHost, st));
+    CC_HIP(hipStreamSynchronize(st));
+    return CC_OK;
+  };
+  KN_TRY(L.start());
+  KN_TRY(L.rank(L.K, ar.at<int32_t>(L.cand), nullptr));
+  KN_TRY(edges());
+  KN_TRY(read());
+  if (h.bad) return non_finite_error();
+  if (h.uncert) {
+    KN_TRY(L.widen());
+    KN_TRY(edges());
+    KN_TRY(read());
+  }
+  const int64_t E = h.total;
+  *n_edges = E;
   if (E > capacity) {
     set_error("edge capacity " + std::to_string(capacity) + " < " + std::to_string(E));
-    *n_edges = E;
     return CC_ERR_INVALID_ARG;
   }
-  hipLaunchKernelGGL(k_emit_edges, dim3((int)cdiv64(n, 256)), dim3(256), 0, st, (int)n, words,
-                     bm.as<uint32_t>(), off.as<int32_t>(), ei, ej);
-  KN_TRY(d2.alloc(E * 8));
+  hipLaunchKernelGGL(k_emit_edges, rows4, dim3(256), 0, st, (int)n, words, ar.at<uint32_t>(bm),
+                     ar.at<int32_t>(off), ei, ej);
   if (E > 0) {
     hipLaunchKernelGGL(k_edge_d2, dim3((int)cdiv64(E, 4)), dim3(256), 0, st, (int)E, (int)p,
-                       Xd.as<double>(), ei, ej, d2.as<double>());
+                       ar.at<double>(L.Xd), ei, ej, ar.at<double>(d2));
   }
-  *n_edges = E;
-  return finish_weights(E, d2.as<double>(), phi, normalize, w, phi_used, st);
+  return finish_weights(E, ar.at<double>(d2), phi, normalize, w, phi_used, ar.at<double>(work), st);
 }
 
 template <typename TI>
 static cc_status min_k_impl(int64_t n, int64_t p, const TI *X, int64_t ldx, const uint8_t *mask,
                             int64_t ldm, int32_t kmax, int32_t *k_min, int32_t *n_comp,
                             hipStream_t st) {
-  DevBuf Xd, knn, ei, ej, keep, lab, ncl;
-  KN_TRY(knn_lists(n, p, X, ldx, mask, ldm, kmax, st, Xd, knn));
+  Arena ar;
+  KnnLists<TI> L{};
+  L.n = n; L.p = p; L.k = kmax; L.X = X; L.ldx = ldx; L.mask = mask; L.ldm = ldm; L.st = st;
+  L.plan(ar);
   const int64_t m = n * kmax;
-  KN_TRY(ei.alloc(m * 4));
-  KN_TRY(ej.alloc(m * 4));
-  KN_TRY(keep.alloc(m));
-  KN_TRY(lab.alloc(n * 4));
-  KN_TRY(ncl.alloc(4));
+  const size_t aei = ar.add(m * 4), aej = ar.add(m * 4), akeep = ar.add(m), alab = ar.add(n * 4), ancl = ar.add(4);
+  KN_TRY(ar.alloc());
+  KN_TRY(L.start());
+  KN_TRY(L.rank(L.K, ar.at<int32_t>(L.cand), nullptr));
+  int32_t h[2] = {0, 0};
+  CC_HIP(hipMemcpyAsync(h, L.bad(), 8, hipMemcpyDeviceToHost, st));
+  CC_HIP(hipStreamSynchronize(st));
+  if (h[0]) return non_finite_error();
+  if (h[1]) KN_TRY(L.widen());
+  int32_t *ei = ar.at<int32_t>(aei), *ej = ar.at<int32_t>(aej), *lab = ar.at<int32_t>(alab), *ncl = ar.at<int32_t>(ancl);
+  uint8_t *keep = ar.at<uint8_t>(akeep);
   hipLaunchKernelGGL(k_knn_pairs, dim3((int)cdiv64(m, 256)), dim3(256), 0, st, (int)n, (int)kmax,
-                     knn.as<int32_t>(), ei.as<int32_t>(), ej.as<int32_t>());
+                     ar.at<int32_t>(L.knn), ei, ej);
   CC_HIP(hipGetLastError());
   // components of the union graph of the first k neighbours
   auto count = [&](int k, int32_t *out) -> cc_status {
     hipLaunchKernelGGL(k_keep_prefix, dim3((int)cdiv64(m, 256)), dim3(256), 0, st, m, (int)kmax, k,
-                       keep.as<uint8_t>());
+                       keep);
     CC_HIP(hipGetLastError());
-    KN_TRY(components(n, m, ei.as<int32_t>(), ej.as<int32_t>(), keep.as<uint8_t>(), nullptr,
-                      lab.as<int32_t>(), ncl.as<int32_t>(), st));
-    CC_HIP(hipMemcpyAsync(out, ncl.p, 4, hipMemcpyDeviceToHost, st));
+    KN_TRY(components(n, m, ei, ej, keep, nullptr, lab, ncl, st));
+    CC_HIP(hipMemcpyAsync(out, ncl, 4, hipMemcpyDeviceToHost, st));
     CC_HIP(hipStreamSynchronize(st));
     return CC_OK;
   };
@@ -811,15 +1182,12 @@ cc_status composite_weights(int64_t n, int64_t n_edges, const int32_t *ei, const
     KN_TRY(bad.alloc(4));
     KN_TRY(Xd.alloc((size_t)n * p * 8));
     CC_HIP(hipMemsetAsync(bad.p, 0, 4, st));
-    const int cb = (int)cdiv64(p, 256), eb = (int)cdiv64(n * p, 256);
+    const int eb = (int)cdiv64(n * p, 256);
+    column_moments(n, p, x_dtype, X, ldx, mask, ldm, true, mean.as<double>(), nullptr, false, bad.as<int>(), st);
     if (x_dtype == CC_DTYPE_F32) {
-      hipLaunchKernelGGL((k_col_moments<float>), dim3(cb), dim3(256), 0, st, (int)n, (int)p, (const float *)X,
-                         ldx, mask, ldm, mean.as<double>(), (double *)nullptr, bad.as<int>());
       hipLaunchKernelGGL((k_impute_d<float>), dim3(eb), dim3(256), 0, st, (int)n, (int)p, (const float *)X, ldx,
                          mask, ldm, mean.as<double>(), Xd.as<double>());
     } else {
-      hipLaunchKernelGGL((k_col_moments<double>), dim3(cb), dim3(256), 0, st, (int)n, (int)p, (const double *)X,
-                         ldx, mask, ldm, mean.as<double>(), (double *)nullptr, bad.as<int>());
       hipLaunchKernelGGL((k_impute_d<double>), dim3(eb), dim3(256), 0, st, (int)n, (int)p, (const double *)X, ldx,
                          mask, ldm, mean.as<double>(), Xd.as<double>());
     }
@@ -827,13 +1195,13 @@ cc_status composite_weights(int64_t n, int64_t n_edges, const int32_t *ei, const
     int hbad = 0;
     CC_HIP(hipMemcpyAsync(&hbad, bad.p, 4, hipMemcpyDeviceToHost, st));
     CC_HIP(hipStreamSynchronize(st));
-    if (hbad) { set_error("observed X has non-finite entries"); return CC_ERR_INVALID_ARG; }
+    if (hbad) return non_finite_error();
     Xuse = Xd.p;
     ldu = p;
     tuse = CC_DTYPE_F64;
   }
   DevBuf d2;
-  KN_TRY(d2.alloc(n_edges * 8));
+  KN_TRY(d2.alloc((n_edges + 2) * 8));
   if (n_edges > 0) {
     const int blocks = (int)cdiv64(n_edges, 4);
     if (tuse == CC_DTYPE_F32)
@@ -844,7 +1212,7 @@ cc_status composite_weights(int64_t n, int64_t n_edges, const int32_t *ei, const
                          (int)p, (const double *)Xuse, ldu, Y, ldy, c, ei, ej, d2.as<double>());
     CC_HIP(hipGetLastError());
   }
-  return finish_weights(n_edges, d2.as<double>(), phi, normalize, w, phi_used, st);
+  return finish_weights(n_edges, d2.as<double>(), phi, normalize, w, phi_used, d2.as<double>() + n_edges, st);
 }
 
 cc_status build_knn_weights(int64_t n, int64_t p, int32_t x_dtype, const void *X, int64_t ldx,
@@ -880,18 +1248,12 @@ cc_status standardize_columns(int64_t n, int64_t p, int32_t x_dtype, void *X, in
   KN_TRY(sd.alloc(p * 8));
   KN_TRY(bad.alloc(4));
   CC_HIP(hipMemsetAsync(bad.p, 0, 4, st));
-  const int cb = (int)cdiv64(p, 256), eb = (int)cdiv64(n * p, 256);
-  if (x_dtype == CC_DTYPE_F32) {
-    hipLaunchKernelGGL((k_col_moments<float>), dim3(cb), dim3(256), 0, st, (int)n, (int)p,
-                       (const float *)X, ldx, mask, ldm, mean.as<double>(), sd.as<double>(), bad.as<int>());
-  } else {
-    hipLaunchKernelGGL((k_col_moments<double>), dim3(cb), dim3(256), 0, st, (int)n, (int)p,
-                       (const double *)X, ldx, mask, ldm, mean.as<double>(), sd.as<double>(), bad.as<int>());
-  }
+  const int eb = (int)cdiv64(n * p, 256);
+  column_moments(n, p, x_dtype, X, ldx, mask, ldm, true, mean.as<double>(), sd.as<double>(), true, bad.as<int>(), st);
   int hbad = 0;
   CC_HIP(hipMemcpyAsync(&hbad, bad.p, 4, hipMemcpyDeviceToHost, st));
   CC_HIP(hipStreamSynchronize(st));
-  if (hbad) { set_error("observed X has non-finite entries"); return CC_ERR_INVALID_ARG; }
+  if (hbad) return non_finite_error();
   if (x_dtype == CC_DTYPE_F32)
     hipLaunchKernelGGL((k_standardize<float>), dim3(eb), dim3(256), 0, st, (int)n, (int)p,
                        (float *)X, ldx, mask, ldm, mean.as<double>(), sd.as<double>());
@@ -964,18 +1326,13 @@ cc_status standardize_columns_noalloc(int64_t n, int64_t p, int32_t x_dtype, voi
   int *bad = reinterpret_cast<int *>(sd + kStdMaxCols);
   // the array keeps the last call's contents: the count starts at zero
   hipLaunchKernelGGL(k_zero_count, dim3(1), dim3(64), 0, st, bad);
-  const int cb = (int)cdiv64(p, 256), eb = (int)cdiv64(n * p, 256);
-  if (x_dtype == CC_DTYPE_F32)
-    hipLaunchKernelGGL((k_col_moments<float>), dim3(cb), dim3(256), 0, st, (int)n, (int)p,
-                       (const float *)X, ldx, mask, ldm, mean, sd, bad);
-  else
-    hipLaunchKernelGGL((k_col_moments<double>), dim3(cb), dim3(256), 0, st, (int)n, (int)p,
-                       (const double *)X, ldx, mask, ldm, mean, sd, bad);
+  const int eb = (int)cdiv64(n * p, 256);
+  column_moments(n, p, x_dtype, X, ldx, mask, ldm, true, mean, sd, true, bad, st);
   CC_HIP(hipGetLastError());
   int hbad = 0;
   CC_HIP(hipMemcpyAsync(&hbad, bad, 4, hipMemcpyDeviceToHost, st));
   CC_HIP(hipStreamSynchronize(st));
-  if (hbad) { set_error("observed X has non-finite entries"); return CC_ERR_INVALID_ARG; }
+  if (hbad) return non_finite_error();
   if (x_dtype == CC_DTYPE_F32)
     hipLaunchKernelGGL((k_standardize<float>), dim3(eb), dim3(256), 0, st, (int)n, (int)p,
                        (float *)X, ldx, mask, ldm, mean, sd);
