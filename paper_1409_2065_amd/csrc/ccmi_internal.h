@@ -72,6 +72,17 @@ struct BatchInst {
 
 enum Prec { kF32 = CC_PREC_F32, kMixed = CC_PREC_MIXED, kF64 = CC_PREC_F64 };
 
+// Small problems: shape of the block that runs a solve's iterations in one
+// workgroup (resident.hip), with the host copies of its tables until they
+// are uploaded.
+struct ResidentPlan {
+  int threads = 0;   // 0: the sweeps run as launches over many blocks
+  int lel = 0;       // log2 of the lanes that share an edge
+  int64_t NE = 0;    // list entries in LDS
+  size_t lds = 0;
+  std::vector<int32_t> estart, order;
+};
+
 struct Problem {
   int64_t n = 0, p = 0, E = 0, ld = 0;
   int precision = kMixed;
@@ -138,6 +149,9 @@ struct Problem {
   DevScalars *sc_host = nullptr; // pinned mirror
   int32_t *flag_host = nullptr;  // pinned
   int32_t *ncl_dev = nullptr;
+  ResidentPlan res;
+  int32_t *res_order = nullptr, *res_estart = nullptr;
+  unsigned long long *res_prof = nullptr;  // sampled ticks: point phase, edge phase, samples
   // host-side constants
   double dev2 = 0.0;   // ||M o (X - xbar)||^2
   double w2 = 0.0;     // sum_e w_e^2
@@ -227,6 +241,10 @@ cc_status hip_fail(hipError_t e, const char *what);
     hipError_t _e = (call);                           \
     if (_e != hipSuccess) return ::ccmi::hip_fail(_e, #call); \
   } while (0)
+
+// ---- small problems in one workgroup (resident.hip) ----
+bool resident_plan(int64_t n, int64_t ld, int64_t E, const int32_t *deg, int prec, ResidentPlan *plan);
+cc_status resident_run(Problem *P, int iters);
 
 // ---- solver (solver.hip) ----
 cc_status problem_create(int64_t n, int64_t p, int32_t x_dtype, const void *X,
