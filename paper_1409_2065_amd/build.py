@@ -12,7 +12,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libccmi.so")
-SOURCES = ["solver.hip", "resident.hip", "knn.hip", "extras.hip", "api.hip"]
+SOURCES = ["solver.hip", "slab.hip", "resident.hip", "knn.hip", "extras.hip", "api.hip"]
 ARCH = os.environ.get("CCMI_OFFLOAD_ARCH", "gfx950")
 
 HIPCC_FLAGS = [
@@ -34,7 +34,7 @@ def hipcc() -> str:
     raise RuntimeError("hipcc not found")
 
 
-def build(verbose: bool = False, jobs: int = 5) -> str:
+def build(verbose: bool = False, jobs: int = 6) -> str:
     """Compile every source to an object, then link libccmi.so.  Always
     recompiles.  Returns the library path."""
     objdir = os.path.join(HERE, "_build")

@@ -83,6 +83,19 @@ struct ResidentPlan {
   std::vector<int32_t> estart, order;
 };
 
+// LDS-slab point sweep (slab.hip): how its blocks split the features and
+// points.
+struct SlabPlan {
+  int blocks = 0;       // 0: the wave-per-item sweep
+  bool forced = false;  // asked for by CCMI_SLAB_F
+  int tiles = 0;        // feature tiles
+  int tpb = 1;          // tiles per block
+  int groups = 1;       // groups of points (each block takes one)
+  int pg = 0;           // points per group
+  size_t lds = 0;
+  std::vector<int32_t> order;  // groups x pg pairs (point, degree) by degree, -1: none
+};
+
 struct Problem {
   int64_t n = 0, p = 0, E = 0, ld = 0;
   int precision = kMixed;
@@ -134,8 +147,9 @@ struct Problem {
   int psweeps = 1;          // projection sweeps per MM iteration (this solve)
   double *H = nullptr;       // several sweeps: h_i = sum_j s_ij (a'_i - a'_j), n x ld FP64
   void *T[2] = {nullptr, nullptr};  // several sweeps: gather copies of the sweeps' increments
-  int slab_f = 0;           // > 0: LDS-slab point sweep with F-feature tiles
-  bool ell_cm = false;      // ELL stored column-major (entry k of i at k*n + i)
+  SlabPlan slab;
+  bool slab_on = false;     // this solve's point sweeps are slab sweeps
+  int32_t *slab_order = nullptr;
   int cur_K = 64;
   double *part = nullptr;    // E x entile edge partials
   double *psum = nullptr;    // point-sweep blocks x 8 point partials
@@ -245,6 +259,12 @@ cc_status hip_fail(hipError_t e, const char *what);
 // ---- small problems in one workgroup (resident.hip) ----
 bool resident_plan(int64_t n, int64_t ld, int64_t E, const int32_t *deg, int prec, ResidentPlan *plan);
 cc_status resident_run(Problem *P, int iters);
+
+// ---- LDS-slab point sweep (slab.hip) ----
+struct PointArgs;
+bool slab_plan(int64_t n, int64_t ld, const int32_t *deg, int prec, SlabPlan *plan);
+void launch_point_slab(Problem *P, const PointArgs &a);
+void launch_slab_start(Problem *P);
 
 // ---- solver (solver.hip) ----
 cc_status problem_create(int64_t n, int64_t p, int32_t x_dtype, const void *X,

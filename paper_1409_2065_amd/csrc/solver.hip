@@ -58,36 +58,6 @@
 namespace ccmi {
 
 // ---------------------------------------------------------------- params
-struct PointArgs {
-  int n, ld, ntile, nitems, chunk;
-  const void *X;
-  const uint8_t *M;
-  void *U;
-  void *A0, *A1, *G0, *G1;
-  void *Usnap, *Asnap;
-  int ell_s;            // ELL stride of the neighbour lists
-  const int32_t *degE, *colE, *eidE;
-  const double *qE;     // mu w / (rho ||b||) of the previous A, per ELL entry
-  const double *s;      // state shrink factors (first iteration of a solve)
-  int K;                // stop-test window
-  int nblk;             // blocks of this problem's launch
-  double *psum;         // this sweep's block partials
-  const double *esum;   // partial rows of the previous edge stage
-  int nrows;            // how many
-  double *trace;
-  const DevScalars *sin;  // scalars of the previous iteration
-  DevScalars *sout;       // advanced scalars (block 0 writes)
-  const BatchInst *bi;    // batched solves only (else null)
-  // several projection sweeps per MM iteration (k_point_rhs only)
-  double *H;              // h_i = sum_j s_ij (a'_i - a'_j), FP64
-  void *T0;               // gather copy of the first sweep's increment A - A'
-  // U stored lazily (k_point only): U is written only at missing entries,
-  // into Umiss at offsets moff[item] + the entry's rank within its item
-  int lazy;
-  void *Umiss;
-  const int32_t *moff;
-};
-
 // Per-edge bookkeeping shared by the fused edge kernel and the reduction
 // kernel: norms, shrink factors, and the q factors of the next iteration.
 struct EdgeState {
@@ -151,11 +121,6 @@ struct ReduceArgs {
   const DevScalars *sc;
 };
 
-// Start of a point sweep: when a sweep is pending, sum the edge stage's
-// partial rows (column-major, the same order in every block) and finish its
-// iteration; block 0 stores the scalars of the iteration about to run (or
-// the final ones) in the other slot.  Blocks of NW waves; red:
-// (NW + 1) * kIterSums.
 // Rank of each missing entry of a work item in the side array of a lazily
 // stored U: entries are numbered by feature slot v, then by lane.  mb[v]
 // holds the ballot of lanes whose slot v is missing.
@@ -166,64 +131,6 @@ __device__ __forceinline__ void miss_ballots(uint32_t mr, bool active, uint64_t 
 }
 __device__ __forceinline__ int lanes_below(uint64_t m) {
   return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-}
-
-// The edge stage's partial rows that a point sweep's block sums first: at
-// most two per thread (blocks of at least 256 threads, at most kEsumRows
-// rows), each 5 aligned 16-byte loads.  They are issued before the sweep's
-// other loads, so that the finish of the previous iteration waits for them
-// alone (loads retire in order); loads are unconditional (row 0 stands in
-// for a missing row and is not added) so that the wait counts stay exact.
-struct EsumLoad {
-  double2 t[2][kEsumStride / 2];
-};
-
-template <int NW>
-__device__ inline void esum_issue(const PointArgs &a, EsumLoad &L) {
-  static_assert(NW * kWave * 2 >= kEsumRows, "at most two partial rows per thread");
-#pragma unroll
-  for (int r = 0; r < 2; ++r) {
-    const int b = threadIdx.x + r * NW * kWave;
-    const double2 *row = reinterpret_cast<const double2 *>(a.esum + (size_t)(b < a.nrows ? b : 0) * kEsumStride);
-#pragma unroll
-    for (int k = 0; k < kEsumStride / 2; ++k) L.t[r][k] = row[k];
-  }
-}
-
-template <int NW, bool BATCH = false>
-__device__ inline DevScalars begin_iteration(const PointArgs &a, double *red, const Blk blk,
-                                             const EsumLoad &L) {
-  double v[kIterSums];
-#pragma unroll
-  for (int q = 0; q < kIterSums; ++q) v[q] = 0.0;
-  // unused when nothing is pending
-#pragma unroll
-  for (int r = 0; r < 2; ++r) {
-    if (threadIdx.x + r * NW * kWave < a.nrows) {
-#pragma unroll
-      for (int k = 0; k < kEsumStride / 2; ++k) {
-        v[2 * k] += L.t[r][k].x;
-        if (2 * k + 1 < kIterSums) v[2 * k + 1] += L.t[r][k].y;
-      }
-    }
-  }
-  DevScalars h = *a.sin;
-  const bool writer = blk.b == 0 && threadIdx.x == 0;
-  if (h.pending && !h.done) {  // uniform
-    block_sum_all<kIterSums, NW>(v, red);
-    finish_scalars(h, v, a.trace, writer);
-    if constexpr (BATCH) {
-      if (h.done) next_gamma(h, *a.bi, blk);
-    }
-  }
-  h.pending = h.done ? 0 : 1;
-  if (!h.done) {
-    h.m_run = h.m;
-    h.pa_run = h.pa;
-    h.theta_run = (h.m > 0) ? h.d_prev / (h.d_prev + h.rho) : 0.0;
-  }
-  if (writer) *a.sout = h;
-  return h;
 }
 
 // ------------------------------------------------------------- k_point
@@ -318,7 +225,7 @@ __device__ __forceinline__ void point_sweep(const PointArgs &a, const Blk blk) {
     if constexpr (PF && VEC == 4) NtIO<TX, 4>::load(X + rowc, x0);
     else RawIO<TX, VEC>::load(X + rowc, x0);
   };
-  EsumLoad el;
+  EsumLoad<NW> el;
   esum_issue<NW>(a, el);
   // waves without an item preload item 0 and never use it
   preload(first < it1 ? first : 0, a.M != nullptr && !lazy, true);
@@ -674,169 +581,6 @@ __global__ __launch_bounds__(kPointBlock) void k_point_batch(const PointArgs *__
   PointArgs a = args[t.x];
   globalize(a);
   point_sweep<PREC, VEC, PF, true>(a, Blk{t.y, a.nblk, xcd_remap(t.y, a.nblk)});
-}
-
-// ------------------------------------------------------- k_point_slab
-// Narrow problems, where an n x F tile of the gather copy fits in LDS: one
-// block per (F-feature tile, 256 points).  The block stages the tile of A'
-// for all n points in LDS once; each lane owns one point, walks its
-// neighbour list (column-major ELL: entry k of point i at k*n + i, so the
-// lanes of a wave read consecutive entries) and gathers neighbour rows from
-// LDS instead of L2.  Same arithmetic as k_point.
-template <int PREC, int F>
-__global__ __launch_bounds__(kBlock) void k_point_slab(PointArgs a) {
-  using TS = typename Traits<PREC>::TS;
-  using TG = typename Traits<PREC>::TG;
-  using TX = typename Traits<PREC>::TX;
-  constexpr int C4 = F / 4;
-  extern __shared__ __align__(16) unsigned char smem[];
-  TG *slab = reinterpret_cast<TG *>(smem);
-  __shared__ double scratch[kWavesPerBlock * kPointSums];
-  __shared__ double red[(kWavesPerBlock + 1) * kIterSums];
-  const Blk blk = hw_blk();
-  EsumLoad el;
-  esum_issue<kWavesPerBlock>(a, el);
-  const DevScalars hs = begin_iteration<kWavesPerBlock>(a, red, blk, el);
-  if (hs.done) return;
-  const int m = hs.m, pa = hs.pa;
-  const double rho = hs.rho, dprev = hs.d_prev;
-  const double theta = hs.theta_run;
-  const int K = a.K;
-  const bool snapU0 = (m == 0), winU = (m > 0) && (m % K == 0);
-  const bool initA = (m == 0) && (K > 1), winA = (m % K) == (K - 1);
-  TS *Us = reinterpret_cast<TS *>(a.Usnap);
-  TS *As = reinterpret_cast<TS *>(a.Asnap);
-  using TA = typename Traits<PREC>::TA;
-  const TA *Ap = reinterpret_cast<const TA *>(pa == 0 ? a.A0 : a.A1);
-  TA *An = reinterpret_cast<TA *>(pa == 0 ? a.A1 : a.A0);
-  const TG *Gp = reinterpret_cast<const TG *>(pa == 0 ? a.G0 : a.G1);
-  TG *Gn = reinterpret_cast<TG *>(pa == 0 ? a.G1 : a.G0);
-  const TX *X = reinterpret_cast<const TX *>(a.X);
-  TS *U = reinterpret_cast<TS *>(a.U);
-
-  const int lb = blk.lb;
-  const int npg = (a.n + kBlock - 1) / kBlock;
-  const int t = lb / npg, g = lb - t * npg;
-  double ps[kPointSums] = {0, 0, 0, 0, 0, 0};
-  if (t < a.ntile) {
-    const int fbase = t * F;
-    // stage the tile of A' (gather copy) for every point
-    for (int idx = threadIdx.x; idx < a.n * C4; idx += blockDim.x) {
-      const int row = idx / C4, c = idx - row * C4;
-      const int f = fbase + 4 * c;
-      TG v[4] = {(TG)0, (TG)0, (TG)0, (TG)0};
-      if (f < a.ld) RawIO<TG, 4>::load(Gp + (size_t)row * a.ld + f, v);
-      TG *dst = slab + (size_t)row * F + 4 * c;
-      dst[0] = v[0]; dst[1] = v[1]; dst[2] = v[2]; dst[3] = v[3];
-    }
-    __syncthreads();
-    const int i = g * kBlock + threadIdx.x;
-    if (i < a.n) {
-      const int deg = a.degE[i];
-      double sumg[F], sumcg[F];
-#pragma unroll
-      for (int f = 0; f < F; ++f) sumg[f] = sumcg[f] = 0.0;
-      double C = 0.0;
-      // neighbours in chunks of 8: the list entries of a chunk are loaded
-      // together, then its rows are read from LDS
-      for (int k0 = 0; k0 < deg; k0 += 8) {
-        int jj[8];
-        double cc[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          jj[u] = i;
-          cc[u] = 0.0;
-          if (k0 + u < deg) {
-            const size_t slot = (size_t)(k0 + u) * a.n + i;
-            jj[u] = a.colE[slot];
-            cc[u] = (m > 0) ? fmin(dprev * a.qE[slot], 1.0) : 1.0 - a.s[a.eidE[slot]];
-          }
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          if (k0 + u < deg) {
-            C += cc[u];
-            const TG *rowj = slab + (size_t)jj[u] * F;
-#pragma unroll
-            for (int f = 0; f < F; ++f) {
-              const double xv = (double)rowj[f];
-              sumg[f] += xv;
-              sumcg[f] = fma(cc[u], xv, sumcg[f]);
-            }
-          }
-        }
-      }
-      const double inv1d = 1.0 / (1.0 + (double)deg);
-      const double S = (double)deg - C;
-#pragma unroll
-      for (int c4 = 0; c4 < C4; ++c4) {
-        const int f0 = fbase + 4 * c4;
-        if (f0 < a.ld) {
-          const size_t row = (size_t)i * a.ld + f0;
-          double ap[4], up[4], x[4], gi[4];
-          bool mk[4] = {true, true, true, true};
-          VecIO<4>::load(Ap + row, ap);
-          VecIO<4>::load(U + row, up);
-          VecIO<4>::load(X + row, x);
-          if (a.M) VecIO<4>::load_mask(a.M + row, mk);
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            gi[v] = (double)slab[(size_t)i * F + 4 * c4 + v];
-            ap[v] = state_value<PREC>(gi[v], ap[v]);
-          }
-          double u[4], an[4], al[4], gn[4];
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            const int f = 4 * c4 + v;
-            double uu;
-            if (m > 0) {
-              const double y = mk[v] ? x[v] : up[v];
-              uu = mm_u(ap[v], theta, y);
-            } else {
-              uu = up[v];
-            }
-            uu = round_to<TS>(uu);
-            const double jac = sumcg[f] - C * gi[v];
-            const double h = S * gi[v] - (sumg[f] - sumcg[f]);
-            double gq, lo;
-            const double anew = state_round<PREC>(ap[v] + (uu - ap[v] + jac) * inv1d, gq, lo);
-            u[v] = uu; an[v] = anew; al[v] = lo; gn[v] = gq;
-            const double dua = uu - anew;
-            ps[0] = fma(dua, dua, ps[0]);
-            if (mk[v]) { const double r = x[v] - uu; ps[3] = fma(r, r, ps[3]); }
-            ps[4] = fma(uu, uu, ps[4]);
-            ps[5] = fma(h, gq, ps[5]);
-          }
-          VecIO<4>::store(U + row, u);
-          if constexpr (Traits<PREC>::hilo) VecIO<4>::store(An + row, al);
-          else VecIO<4>::store(An + row, an);
-          if (Traits<PREC>::mirror) VecIO<4>::store(Gn + row, gn);
-          if (winU) {
-            double us[4];
-            VecIO<4>::load(Us + row, us);
-#pragma unroll
-            for (int v = 0; v < 4; ++v) { const double du = u[v] - us[v]; ps[2] = fma(du, du, ps[2]); }
-          }
-          if (snapU0 || winU) VecIO<4>::store(Us + row, u);
-          if (initA) VecIO<4>::store(As + row, ap);
-          if (winA) {
-            double prev[4];
-            if (m == 0) {
-#pragma unroll
-              for (int v = 0; v < 4; ++v) prev[v] = ap[v];
-            } else {
-              VecIO<4>::load(As + row, prev);
-            }
-#pragma unroll
-            for (int v = 0; v < 4; ++v) { const double da = an[v] - prev[v]; ps[1] = fma(da, da, ps[1]); }
-            VecIO<4>::store(As + row, an);
-          }
-        }
-      }
-    }
-  }
-  const double tot = block_sum<kPointSums>(ps, scratch);
-  if (threadIdx.x < kPointSums) a.psum[(size_t)lb * 8 + threadIdx.x] = tot;
 }
 
 // ------------------------------------------------------------- k_jacobi
@@ -1739,7 +1483,7 @@ __global__ __launch_bounds__(1024) void k_components(int n, int E, const int32_t
 // ====================================================================== host
 static inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-constexpr int64_t kSlabBytes = 128 * 1024;  // LDS budget of the slab point sweep
+constexpr int64_t kSlabBytes = 128 * 1024;  // LDS budget of the slab sweeps
 
 static size_t ts_size(int prec) { return prec == kF32 ? 4 : 8; }
 static size_t tx_size(int prec) { return prec == kF64 ? 8 : 4; }
@@ -1778,18 +1522,6 @@ static hipEvent_t *prof_slot(Problem *P) {
     P->prof_events.push_back(ev);
   }
   return &P->prof_events[4 * P->prof_used++];
-}
-
-// Launch on a stream.  With events given, hipExtLaunchKernel stamps them with
-// the kernel's own start (e0) and end (e1), so a sampled duration is the
-// kernel's execution, not the gap between two markers around it.
-template <typename... KArgs, typename... Args>
-static void klaunch(void (*kernel)(KArgs...), dim3 grid, dim3 block, size_t lds, hipStream_t stream,
-                    hipEvent_t e0, hipEvent_t e1, Args... args) {
-  if (e0 || e1)
-    hipExtLaunchKernelGGL(kernel, grid, block, (uint32_t)lds, stream, e0, e1, 0u, args...);
-  else
-    hipLaunchKernelGGL(kernel, grid, block, lds, stream, args...);
 }
 
 // Arguments of a point sweep: it reads the current scalar slot and writes the
@@ -1961,13 +1693,6 @@ static void launch_edge_p(Problem *P, int init, int nbp) {
   klaunch(k_edge_reduce, dim3(rblocks), dim3(kEdgeBlock), 0, P->stream, nullptr, P->pev[3], ra);
 }
 
-template <int PREC, int F>
-static void launch_point_slab_t(Problem *P, int blocks) {
-  const PointArgs pa = point_args(P, Launch{blocks, 0, 0});
-  const size_t lds = (size_t)P->n * F * sizeof(typename Traits<PREC>::TG);
-  klaunch(k_point_slab<PREC, F>, dim3(blocks), dim3(kBlock), lds, P->stream, P->pev[0], P->pev[1], pa);
-}
-
 template <int PREC>
 static void set_slab_attr() {
   (void)hipFuncSetAttribute((const void *)k_edge_slab<PREC, 4>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSlabBytes);
@@ -1992,20 +1717,13 @@ static Launch point_grid(const Problem *P) {
 
 // Blocks of the point sweep (its partials count).
 static int point_blocks(Problem *P) {
-  if (P->slab_f > 0) return (int)(cdiv(P->ntile * cdiv(P->n, kBlock), kXcds) * kXcds);
-  return point_grid(P).blocks;
+  return P->slab_on ? P->slab.blocks : point_grid(P).blocks;
 }
 
 template <int PREC>
 static void launch_point_p(Problem *P, const Launch &Lp) {
-  if (P->slab_f > 0) {
-    const int blocks = point_blocks(P);
-    switch (P->slab_f) {
-      case 4: launch_point_slab_t<PREC, 4>(P, blocks); break;
-      case 8: launch_point_slab_t<PREC, 8>(P, blocks); break;
-      case 16: launch_point_slab_t<PREC, 16>(P, blocks); break;
-      default: launch_point_slab_t<PREC, 32>(P, blocks); break;
-    }
+  if (P->slab_on) {
+    launch_point_slab(P, point_args(P, Launch{P->slab.blocks, 0, 0}));
     return;
   }
   switch (P->vec) {
@@ -2101,7 +1819,7 @@ void problem_free(Problem *P) {
                   P->itemI, P->itemJ, P->itemE,
                   P->ei, P->ej, P->w, P->s, P->nb[0], P->nb[1], P->qe, P->qE, P->epos, P->degE, P->colE,
                   P->eidE, P->part, P->psum,
-                  P->esum, P->trace, P->sc, P->ncl_dev, P->res_order, P->res_estart, P->res_prof, P->H, P->T[0], P->T[1], P->Umiss, P->moff};
+                  P->esum, P->trace, P->sc, P->ncl_dev, P->res_order, P->res_estart, P->res_prof, P->slab_order, P->H, P->T[0], P->T[1], P->Umiss, P->moff};
   for (void *b : bufs)
     if (b) (void)hipFree(b);
   if (Traits<kMixed>::mirror && P->precision == kMixed) {
@@ -2133,20 +1851,8 @@ static cc_status dmalloc(void **p, size_t bytes) {
   } while (0)
 
 static void choose_tiles(Problem *P) {
-  // point sweep: the LDS slab variant when an n x F tile of the gather copy
-  // fits (F = 32, 16, 8 or 4 features), else a wave per (point, 64*vec tile)
-  // The wave kernel is the default: the slab variant runs one wave per SIMD
-  // and measured slower on both the p = 500 and the p = 20000 workloads; it
-  // is kept as an option (CCMI_SLAB_F = 4, 8, 16 or 32).
   const int64_t tg = (P->precision == kF64) ? 8 : 4;
-  int slab = 0;
-  const char *es = getenv("CCMI_SLAB_F");
-  if (es) slab = atoi(es);
-  if (slab != 4 && slab != 8 && slab != 16 && slab != 32) slab = 0;
-  if (slab > 0 && P->n * slab * tg > kSlabBytes) slab = 0;
-  P->slab_f = slab;
-  P->ell_cm = slab > 0;
-  // edge sweep over wide rows: LDS tile width (independent of the above)
+  // edge sweep over wide rows: LDS tile width
   P->edge_f = 0;
   for (int f : {16, 8, 4}) {
     if (P->n * f * tg <= kSlabBytes / 2) { P->edge_f = f; break; }
@@ -2165,7 +1871,7 @@ static void choose_tiles(Problem *P) {
   const char *eiw = getenv("CCMI_EDGE_IPW");
   const int eipw = eiw ? atoi(eiw) : P->ipw;
   P->eipw = (eipw == 2 || eipw == 4) ? eipw : 1;
-  P->tile_w = slab > 0 ? slab : kWave * vec;
+  P->tile_w = kWave * vec;
   P->ntile = (int)cdiv(P->ld, P->tile_w);
   // waves per block of the point sweep (CCMI_POINT_WAVES = 4, 8 or 16; the
   // wider blocks for the mixed precision with 4 features per lane).  With
@@ -2259,7 +1965,7 @@ cc_status problem_create(int64_t n, int64_t p, int32_t x_dtype, const void *X,
   P->n = n; P->p = p; P->E = n_edges; P->ld = (p + 3) / 4 * 4;
   P->precision = precision; P->stream = stream; P->has_mask = mask != nullptr;
   choose_tiles(P);
-  if (P->slab_f > 0 || P->eslab) {
+  if (P->eslab) {
     if (precision == kF32) set_slab_attr<kF32>();
     else if (precision == kF64) set_slab_attr<kF64>();
     else set_slab_attr<kMixed>();
@@ -2295,7 +2001,7 @@ cc_status problem_create(int64_t n, int64_t p, int32_t x_dtype, const void *X,
   CC_TRY(dmalloc((void **)&P->epos, 2 * E * 4));
   CC_TRY(dmalloc((void **)&P->part, E * (P->efused ? 1 : P->entile) * 8));
   // one row of point partials per block of the point sweep
-  CC_TRY(dmalloc((void **)&P->psum, std::max<int64_t>(kMaxBlocks, point_blocks(P)) * 8 * 8));
+  CC_TRY(dmalloc((void **)&P->psum, kMaxBlocks * 8 * 8));
   CC_TRY(dmalloc((void **)&P->esum, (size_t)kEsumRows * kEsumStride * 8));
   CC_TRY(dmalloc((void **)&P->sc, 2 * sizeof(DevScalars)));
   CC_TRY(dmalloc((void **)&P->ncl_dev, 4));
@@ -2360,7 +2066,12 @@ cc_status problem_create(int64_t n, int64_t p, int32_t x_dtype, const void *X,
     }
   }
   P->nbe = edge_rows(P);
-  if (P->slab_f == 0 && resident_plan(n, P->ld, E, deg.data(), precision, &P->res)) {
+  if (slab_plan(n, P->ld, deg.data(), precision, &P->slab)) {
+    const size_t bytes = P->slab.order.size() * 4;
+    CC_TRY(dmalloc((void **)&P->slab_order, bytes));
+    CC_HIP(hipMemcpyAsync(P->slab_order, P->slab.order.data(), bytes, hipMemcpyHostToDevice, stream));
+  }
+  if (!P->slab.forced && resident_plan(n, P->ld, E, deg.data(), precision, &P->res)) {
     CC_TRY(dmalloc((void **)&P->res_order, n * 4));
     CC_TRY(dmalloc((void **)&P->res_estart, n * 4));
     CC_TRY(dmalloc((void **)&P->res_prof, 3 * 8));
@@ -2369,7 +2080,8 @@ cc_status problem_create(int64_t n, int64_t p, int32_t x_dtype, const void *X,
     CC_HIP(hipMemsetAsync(P->res_prof, 0, 3 * 8, stream));
   }
   // ELL copy of the neighbour lists for the point sweep
-  const int64_t S = std::max<int64_t>(maxdeg, 1);
+  // (the stride a multiple of 4: the slab sweep reads four entries at a time)
+  const int64_t S = (std::max<int64_t>(maxdeg, 1) + 3) / 4 * 4;
   // the sweeps index ELL slots (n * S of them) in 32 bits: checked before
   // any of the n * S host or device arrays exists
   if (n * S > ((int64_t)1 << 31) - 1) {
@@ -2379,9 +2091,7 @@ cc_status problem_create(int64_t n, int64_t p, int32_t x_dtype, const void *X,
   P->ell_s = (int)S;
   // unused slots: column -1 (the wave sweep counts neighbours by it), edge 0
   std::vector<int32_t> hdegE(n), hcolE(n * S, -1), heidE(n * S, 0), hposE(2 * E);
-  // row-major (entry k of i at i*S + k) for the wave-per-point sweep,
-  // column-major (k*n + i) for the slab sweep
-  auto ell_slot = [&](int64_t i, int64_t k) -> int64_t { return P->ell_cm ? k * n + i : i * S + k; };
+  auto ell_slot = [&](int64_t i, int64_t k) -> int64_t { return i * S + k; };
   for (int64_t i = 0; i < n; ++i) {
     hdegE[i] = rp[i + 1] - rp[i];
     for (int32_t k = rp[i]; k < rp[i + 1]; ++k) {
@@ -2575,7 +2285,7 @@ cc_status solve(Problem *P, double gamma, const cc_solve_opts &o, cc_solve_info 
     set_error("proj_sweeps must be in 1.." + std::to_string(kMaxProjSweeps));
     return CC_ERR_INVALID_ARG;
   }
-  if (o.proj_sweeps > 1 && P->slab_f > 0) {
+  if (o.proj_sweeps > 1 && P->slab.forced) {
     set_error("proj_sweeps > 1 needs the wave point sweep (not the LDS-slab option)");
     return CC_ERR_INVALID_ARG;
   }
@@ -2594,8 +2304,10 @@ cc_status solve(Problem *P, double gamma, const cc_solve_opts &o, cc_solve_info 
   const char *lz = getenv("CCMI_LAZY_U");
   const int lzmode = lz ? atoi(lz) : 1;
   const bool resident = P->res.threads > 0 && P->psweeps == 1;
-  P->lazy_u = !resident && P->psweeps == 1 && P->slab_f == 0 && lzmode != 0 &&
-              (!P->M || lzmode == 2 || point_grid(P).chunk > point_waves(P));
+  // the slab sweep, unless a storage switch asks for the wave sweep's choice
+  P->slab_on = !resident && P->psweeps == 1 && P->slab.blocks > 0 && (P->slab.forced || !lz);
+  P->lazy_u = !resident && P->psweeps == 1 && lzmode != 0 &&
+              (!P->M || (!P->slab_on && (lzmode == 2 || point_grid(P).chunk > point_waves(P))));
   if (P->lazy_u && P->M && (!P->moff || P->moff_vec != P->vec)) {
     if (build_miss_index(P) != CC_OK) P->lazy_u = false;  // store U every iteration
   }
@@ -2618,6 +2330,10 @@ cc_status solve(Problem *P, double gamma, const cc_solve_opts &o, cc_solve_info 
   hipLaunchKernelGGL(k_set_params, dim3(1), dim3(1), 0, P->stream, P->sc + P->slot, gamma, rho,
                      eps, thr, o.max_iter, record, o.test_every);
   CC_HIP(hipGetLastError());
+  if (P->slab_on) {
+    launch_slab_start(P);
+    CC_HIP(hipGetLastError());
+  }
   const int check = std::max(1, o.check_every);
   // sweeps m = 0 .. max_iter, each finished by the next launch pair; the
   // last pair only finishes (the stop rule ends the solve by then)
@@ -2927,6 +2643,7 @@ static cc_status build_launch_set(LaunchSet &L, const std::vector<Problem *> &pr
     // following the point sweep)
     P->eipw = kBatchEdgeItems;
     P->nbe = edge_rows(P);
+    P->slab_on = false;
     const Launch Lp = sweep_grid(P->n * P->ntile, kPointWaves, P->ipw);
     const Launch Li = edge_items_grid(P->n_items, P->eipw);
     pblocks[b] = Lp.blocks;
@@ -3089,7 +2806,7 @@ cc_status batch_create(int32_t n_inst, Problem *const *probs, const int32_t *n_g
     const Problem *P = probs[b];
     if (!P) { set_error("problem " + std::to_string(b) + " is NULL"); return CC_ERR_INVALID_ARG; }
     if (P->precision != probs[0]->precision) { set_error("all problems of a batch need the same precision"); return CC_ERR_INVALID_ARG; }
-    if (!P->eitems || P->slab_f > 0) {
+    if (!P->eitems || P->slab.forced) {
       set_error("problem " + std::to_string(b) + ": rows wider than a batched sweep takes (p <= 1024)");
       return CC_ERR_INVALID_ARG;
     }

@@ -3,6 +3,8 @@
 // the end of an MM iteration.
 #pragma once
 
+#include <hip/hip_ext.h>
+
 #include "ccmi_internal.h"
 #include "wave_ops.h"
 
@@ -261,6 +263,37 @@ __device__ inline Blk hw_blk() {
   return Blk{b, nb, xcd_remap(b, nb)};
 }
 
+// ---------------------------------------------------------------- params
+struct PointArgs {
+  int n, ld, ntile, nitems, chunk;
+  const void *X;
+  const uint8_t *M;
+  void *U;
+  void *A0, *A1, *G0, *G1;
+  void *Usnap, *Asnap;
+  int ell_s;            // ELL stride of the neighbour lists
+  const int32_t *degE, *colE, *eidE;
+  const double *qE;     // mu w / (rho ||b||) of the previous A, per ELL entry
+  const double *s;      // state shrink factors (first iteration of a solve)
+  int K;                // stop-test window
+  int nblk;             // blocks of this problem's launch
+  double *psum;         // this sweep's block partials
+  const double *esum;   // partial rows of the previous edge stage
+  int nrows;            // how many
+  double *trace;
+  const DevScalars *sin;  // scalars of the previous iteration
+  DevScalars *sout;       // advanced scalars (block 0 writes)
+  const BatchInst *bi;    // batched solves only (else null)
+  // several projection sweeps per MM iteration (k_point_rhs only)
+  double *H;              // h_i = sum_j s_ij (a'_i - a'_j), FP64
+  void *T0;               // gather copy of the first sweep's increment A - A'
+  // U stored lazily (k_point only): U is written only at missing entries,
+  // into Umiss at offsets moff[item] + the entry's rank within its item
+  int lazy;
+  void *Umiss;
+  const int32_t *moff;
+};
+
 // ------------------------------------------------------- iteration finish
 // End of MM iteration h.m from the full sums v (point sums, then edge sums):
 // d, the objective, the windowed stop test and the advance of the scalars.
@@ -339,6 +372,83 @@ __device__ inline void next_gamma(DevScalars &h, const BatchInst &bi, const Blk 
 // kernel that forms or rebuilds u rounds it the same way.
 __device__ __forceinline__ double mm_u(double ap, double theta, double y) {
   return fma(theta, y - ap, ap);
+}
+
+// The edge stage's partial rows that a point sweep's block sums first (at
+// most kEsumRows: one or two per thread), each 5 aligned 16-byte loads.  They are issued before the sweep's
+// other loads, so that the finish of the previous iteration waits for them
+// alone (loads retire in order); loads are unconditional (row 0 stands in
+// for a missing row and is not added) so that the wait counts stay exact.
+template <int NW> struct EsumLoad {
+  static constexpr int kRows = (kEsumRows + NW * kWave - 1) / (NW * kWave);  // per thread
+  double2 t[kRows][kEsumStride / 2];
+};
+
+template <int NW>
+__device__ inline void esum_issue(const PointArgs &a, EsumLoad<NW> &L) {
+#pragma unroll
+  for (int r = 0; r < EsumLoad<NW>::kRows; ++r) {
+    const int b = threadIdx.x + r * NW * kWave;
+    const double2 *row = reinterpret_cast<const double2 *>(a.esum + (size_t)(b < a.nrows ? b : 0) * kEsumStride);
+#pragma unroll
+    for (int k = 0; k < kEsumStride / 2; ++k) L.t[r][k] = row[k];
+  }
+}
+
+// Start of a point sweep: when a sweep is pending, sum the edge stage's
+// partial rows (column-major, the same order in every block) and finish its
+// iteration; block 0 stores the scalars of the iteration about to run (or
+// the final ones) in the other slot.  Blocks of NW waves; red:
+// (NW + 1) * kIterSums.
+template <int NW, bool BATCH = false>
+__device__ inline DevScalars begin_iteration(const PointArgs &a, double *red, const Blk blk,
+                                             const EsumLoad<NW> &L) {
+  double v[kIterSums];
+#pragma unroll
+  for (int q = 0; q < kIterSums; ++q) v[q] = 0.0;
+  // unused when nothing is pending
+#pragma unroll
+  for (int r = 0; r < EsumLoad<NW>::kRows; ++r) {
+    if (threadIdx.x + r * NW * kWave < a.nrows) {
+#pragma unroll
+      for (int k = 0; k < kEsumStride / 2; ++k) {
+        v[2 * k] += L.t[r][k].x;
+        if (2 * k + 1 < kIterSums) v[2 * k + 1] += L.t[r][k].y;
+      }
+    }
+  }
+  DevScalars h = *a.sin;
+  const bool writer = blk.b == 0 && threadIdx.x == 0;
+  if (h.pending && !h.done) {  // uniform
+    block_sum_all<kIterSums, NW>(v, red);
+    // uniform, and known to be: the scalars' branches and integers stay scalar
+#pragma unroll
+    for (int q = 0; q < kIterSums; ++q) v[q] = readlane_d(v[q], 0);
+    finish_scalars(h, v, a.trace, writer);
+    if constexpr (BATCH) {
+      if (h.done) next_gamma(h, *a.bi, blk);
+    }
+  }
+  h.pending = h.done ? 0 : 1;
+  if (!h.done) {
+    h.m_run = h.m;
+    h.pa_run = h.pa;
+    h.theta_run = (h.m > 0) ? h.d_prev / (h.d_prev + h.rho) : 0.0;
+  }
+  if (writer) *a.sout = h;
+  return h;
+}
+
+// Launch on a stream.  With events given, hipExtLaunchKernel stamps them with
+// the kernel's own start (e0) and end (e1), so a sampled duration is the
+// kernel's execution, not the gap between two markers around it.
+template <typename... KArgs, typename... Args>
+static void klaunch(void (*kernel)(KArgs...), dim3 grid, dim3 block, size_t lds, hipStream_t stream,
+                    hipEvent_t e0, hipEvent_t e1, Args... args) {
+  if (e0 || e1)
+    hipExtLaunchKernelGGL(kernel, grid, block, (uint32_t)lds, stream, e0, e1, 0u, args...);
+  else
+    hipLaunchKernelGGL(kernel, grid, block, lds, stream, args...);
 }
 
 }  // namespace ccmi
