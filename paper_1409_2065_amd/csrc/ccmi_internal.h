@@ -112,6 +112,7 @@ struct Problem {
   bool eitems = false;       // rows up to 512 wide: edge work items by lower end
   int item_nv = 8;           // features per lane of the item edge sweep
   int64_t n_items = 0;       // edge work items (up to kItemEdges edges each)
+  int erows = 0;             // wide rows, few edges: waves per edge over the whole row (0: not)
   bool eslab = false;        // wide rows, small n: LDS-slab edge sweep
   bool eslab_items = false;  // the slab sweep takes edges in work items
   // U stored lazily (single solves with one projection sweep): the point

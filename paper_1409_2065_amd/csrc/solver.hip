@@ -1037,6 +1037,71 @@ __global__ __launch_bounds__(kEdgeBlock) void k_edge_items_batch(const EdgeArgs 
   edge_items_sweep<PREC, NV>(a, Blk{t.y, a.nblk, xcd_remap(t.y, a.nblk)});
 }
 
+// Wide rows, few edges: WPE waves (1, or a whole block) take one edge over the
+// whole row, so the stage is one launch and leaves no partials for a second
+// one.  A lane reads both rows four features at a time, kRowChunks of each in
+// flight.  At 52 x 4682 (about 170 edges, 6 MB of rows from L2) the stage takes
+// 6 us by blocks, against 15.7 for the slab sweep and its reduction.
+constexpr int kRowChunks = 4;
+
+template <int PREC, int WPE>
+__global__ __launch_bounds__(kEdgeBlock) void k_edge_rows(EdgeArgs a) {
+  using TG = typename Traits<PREC>::TG;
+  __shared__ double wsum[kEdgeWaves];
+  const DevScalars *sc = a.sc;
+  if (!a.init && sc->done) return;
+  const Blk blk = hw_blk();
+  const double pmine = a.init ? 0.0 : point_partial_load(a.psum, a.nbp, blk);
+  const int pa = sc->pa;
+  const int buf = a.init ? pa : (pa ^ 1);
+  const TG *Gc = reinterpret_cast<const TG *>(buf == 0 ? a.G0 : a.G1);
+  const int lane = threadIdx.x % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  constexpr int EPB = kEdgeWaves / WPE;  // edges a block takes at once
+  constexpr int STEP = 4 * kWave * WPE;  // features one load of the edge's lanes covers
+  const int first = WPE == 1 ? wave : 0, l0 = 4 * (WPE == 1 ? lane : (int)threadIdx.x);
+  double t3[kEdgeSums] = {0.0, 0.0, 0.0};
+  for (int e0 = blk.lb * EPB; e0 < a.es.E; e0 += blk.nb * EPB) {
+    const int e = e0 + first;
+    const bool ok = e < a.es.E;
+    const int ec = ok ? e : 0;
+    const TG *gi = Gc + (size_t)a.ei[ec] * a.ld, *gj = Gc + (size_t)a.ej[ec] * a.ld;
+    EdgeIn in{0.0, 0.0, 0.0, 0.0, 0.0, 0, 0};
+    if (!a.init) in = edge_prefetch(a.es, ec);
+    double acc = 0.0;
+    for (int f0 = l0; f0 - l0 < a.ld; f0 += kRowChunks * STEP) {
+      TG ri[kRowChunks][4], rj[kRowChunks][4];
+#pragma unroll
+      for (int c = 0; c < kRowChunks; ++c) {
+        const int f = f0 + c * STEP;
+        RawIO<TG, 4>::load(gi + (f < a.ld ? f : 0), ri[c]);
+        RawIO<TG, 4>::load(gj + (f < a.ld ? f : 0), rj[c]);
+      }
+#pragma unroll
+      for (int c = 0; c < kRowChunks; ++c) {
+        const bool in_row = f0 + c * STEP < a.ld;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const double d = in_row ? (double)ri[c][v] - (double)rj[c][v] : 0.0;
+          acc = fma(d, d, acc);
+        }
+      }
+    }
+    acc = wave_sum(acc);
+    if constexpr (WPE > 1) {
+      if (lane == 0) wsum[wave] = acc;
+      __syncthreads();
+      acc = 0.0;
+#pragma unroll
+      for (int w = 0; w < kEdgeWaves; ++w) acc += wsum[w];
+      __syncthreads();  // read before the next edge's sums are written
+    }
+    if (ok && (WPE == 1 ? lane : (int)threadIdx.x) == 0) edge_update(a.es, e, acc, in, a.init, pa, sc, t3);
+  }
+  if (a.init) return;
+  edge_block_partials(t3, point_partial_sum(pmine, a.psum, a.nbp, blk), a.esum, blk);
+}
+
 // Wide rows: one wave per (point i, 256-feature tile); each quarter-wave
 // takes one upper neighbour j > i (so a_i is read once per point and tile)
 // and writes the tile's partial (a_i - a_j)^2 for k_edge_reduce.
@@ -1494,6 +1559,10 @@ struct Launch {
   int blocks, chunk, nitems;
 };
 
+// Most bytes of rows for which the edge stage over wide rows takes whole rows
+// (4-byte and 8-byte gather copies).
+constexpr int64_t kEdgeRowBytes4 = (int64_t)384 << 20, kEdgeRowBytes8 = (int64_t)256 << 20;
+
 // Grid for a sweep over nitems wave-items with `waves` waves per block and
 // about ipw items per wave: at most kMaxBlocks blocks, a multiple of the XCD
 // count, each block owning a contiguous chunk.
@@ -1634,6 +1703,10 @@ static int edge_reduce_blocks(int64_t E) {
 // Partial rows the edge stage leaves for the next point sweep.
 static int edge_rows(Problem *P) {
   if (P->eitems) return edge_items_grid(P->n_items, P->eipw).blocks;
+  if (P->erows > 0) {
+    const int64_t per = P->erows == 1 ? kEdgeWaves : 1;
+    return (int)std::min<int64_t>(std::max<int64_t>(cdiv(P->E, per), 1), kEsumRows);
+  }
   return P->efused ? edge_fused_grid(P->E).blocks : edge_reduce_blocks(P->E);
 }
 
@@ -1661,6 +1734,15 @@ static void launch_edge_p(Problem *P, int init, int nbp) {
       case 8: klaunch(k_edge_fused<PREC, 8>, dim3(Le.blocks), dim3(kEdgeBlock), 0, P->stream, P->pev[2], P->pev[3], ea); break;
       default: klaunch(k_edge_fused<PREC, 16>, dim3(Le.blocks), dim3(kEdgeBlock), 0, P->stream, P->pev[2], P->pev[3], ea); break;
     }
+    return;
+  }
+  if (P->erows > 0) {
+    const int blocks = edge_rows(P);
+    const EdgeArgs ea = edge_args(P, Launch{blocks, 0, 0}, init, nbp);
+    if (P->erows == 1)
+      klaunch(k_edge_rows<PREC, 1>, dim3(blocks), dim3(kEdgeBlock), 0, P->stream, P->pev[2], P->pev[3], ea);
+    else
+      klaunch(k_edge_rows<PREC, kEdgeWaves>, dim3(blocks), dim3(kEdgeBlock), 0, P->stream, P->pev[2], P->pev[3], ea);
     return;
   }
   if (P->eslab && P->eslab_items) {
@@ -1902,7 +1984,17 @@ static void choose_tiles(Problem *P) {
     // small n: stage tiles in LDS and keep per-edge accumulators in registers
     const char *ee = getenv("CCMI_EDGE_SLAB");
     const bool allow = !ee || atoi(ee) != 0;
-    if (allow && P->edge_f > 0 && P->E <= 1024 * 16 && P->n * (P->edge_f / 4) <= kSlabChunks * 1024 && P->n < 65536) {
+    // whole rows, one launch, while the rows read (2 per edge) cost the L2s
+    // less than staging and reducing slabs does: at 289 MB (1000 x 3000, 12 000
+    // edges) 22.5 against 39.4 us, at 395 MB (1000 x 6000) 32.3 and 37.7; FP64
+    // at 236 MB (300 x 8000) 19.7 and 19.0.  A block per edge where edges are
+    // few against the row's length (170 edges of 4682 features: 5.2 us, by
+    // waves 8.5), else a wave (650 of 1100: 5.5 us, by blocks 8.6)
+    if (!ee && !getenv("CCMI_EDGE_SLAB_ITEMS") &&
+        2 * P->E * P->ld * tg <= (tg == 4 ? kEdgeRowBytes4 : kEdgeRowBytes8)) {
+      P->erows = 16 * P->E <= P->ld ? kEdgeWaves : 1;
+      P->entile = 1;
+    } else if (allow && P->edge_f > 0 && P->E <= 1024 * 16 && P->n * (P->edge_f / 4) <= kSlabChunks * 1024 && P->n < 65536) {
       P->eslab = true;
       P->eslab_ntf = (int)cdiv(P->ld, P->edge_f);
       P->eslab_tpg = (int)cdiv(P->eslab_ntf, 256);
@@ -1999,7 +2091,7 @@ cc_status problem_create(int64_t n, int64_t p, int32_t x_dtype, const void *X,
   CC_TRY(dmalloc((void **)&P->nb[1], E * 8));
   CC_TRY(dmalloc((void **)&P->qe, E * 8));
   CC_TRY(dmalloc((void **)&P->epos, 2 * E * 4));
-  CC_TRY(dmalloc((void **)&P->part, E * (P->efused ? 1 : P->entile) * 8));
+  CC_TRY(dmalloc((void **)&P->part, E * (P->efused || P->erows ? 1 : P->entile) * 8));
   // one row of point partials per block of the point sweep
   CC_TRY(dmalloc((void **)&P->psum, kMaxBlocks * 8 * 8));
   CC_TRY(dmalloc((void **)&P->esum, (size_t)kEsumRows * kEsumStride * 8));

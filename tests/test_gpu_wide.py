@@ -1,6 +1,7 @@
 """Wide rows: the LDS-slab point sweep (tiles of 32 features, groups of
-points, several tiles per block, lists of 0 to more than 64 neighbours),
-against the oracle's FP64 trajectory: 1e-11 relative for FP64 states, 2e-6 and 2e-5 for
+points, several tiles per block, lists of 0 to more than 64 neighbours) and
+the edge sweep over whole rows (a wave or a block per edge), against the
+oracle's FP64 trajectory: 1e-11 relative for FP64 states, 2e-6 and 2e-5 for
 the mixed and FP32 states over these few iterations."""
 import numpy as np
 import pytest
@@ -82,3 +83,12 @@ def test_slab_warm_starts(cc, monkeypatch, precision):
     tol = {"f32": 2e-5, "mixed": 2e-6, "f64": 1e-11}[precision]
     for a, b in zip(*out):
         assert rel_max(a, b) < tol
+
+
+# a block per edge (few edges, long rows) and a wave per edge; rows beyond a
+# lane's first chunks, ragged ends, more edges than partial rows
+@pytest.mark.parametrize("n,p,k,precision,tol", [(2, 1025, 1, "f64", 1e-11), (12, 1500, 2, "f64", 1e-11),
+                                                 (12, 9000, 2, "f64", 1e-11), (40, 1025, 6, "f64", 1e-11),
+                                                 (120, 1203, 20, "f64", 1e-11), (150, 2051, 9, "mixed", 2e-6)])
+def test_edge_rows(cc, n, p, k, precision, tol):
+    follow(cc, *problem(n, p, k, n % 4 == 0), precision, 3.0, 15, tol)
