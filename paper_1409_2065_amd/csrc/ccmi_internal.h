@@ -197,7 +197,7 @@ struct PointClass {
   int2 *ptab = nullptr;
 };
 struct EdgeClass {
-  int nv = 1, nblk = 0;
+  int nv = 1, nblk = 0;  // nv 0: every width in one launch
   EdgeArgs *eargs[2] = {nullptr, nullptr};
   int2 *etab = nullptr;
 };

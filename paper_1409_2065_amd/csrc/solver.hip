@@ -1037,6 +1037,31 @@ __global__ __launch_bounds__(kEdgeBlock) void k_edge_items_batch(const EdgeArgs 
   edge_items_sweep<PREC, NV>(a, Blk{t.y, a.nblk, xcd_remap(t.y, a.nblk)});
 }
 
+// Served rounds: instances of every width in one launch, the features per
+// lane packed with the local block (kNvShift).  A round's launches follow
+// each other on one stream, where a launch per width left most of the chip
+// idle in each (12 requests of four widths: 18.7 + 13.4 + 11.8 + 11.7 us, here
+// 24).  A batch's graph runs the widths as parallel branches instead, in
+// kernels that fit more waves per SIMD (48 instances: 29 us, here 33).
+constexpr int kNvShift = 16;
+
+template <int PREC>
+__global__ __launch_bounds__(kEdgeBlock) __attribute__((amdgpu_waves_per_eu(PREC == kF64 ? 1 : 4))) void k_edge_items_any(
+    const EdgeArgs *__restrict__ args, const int2 *__restrict__ tab) {
+  const int2 t = tab[blockIdx.x];
+  EdgeArgs a = args[t.x];
+  globalize(a);
+  const int b = t.y & ((1 << kNvShift) - 1);
+  const Blk blk{b, a.nblk, xcd_remap(b, a.nblk)};
+  switch (__builtin_amdgcn_readfirstlane(t.y >> kNvShift)) {
+    case 1: edge_items_sweep<PREC, 1>(a, blk); break;
+    case 2: edge_items_sweep<PREC, 2>(a, blk); break;
+    case 4: edge_items_sweep<PREC, 4>(a, blk); break;
+    case 8: edge_items_sweep<PREC, 8>(a, blk); break;
+    default: edge_items_sweep<PREC, 16>(a, blk); break;
+  }
+}
+
 // Wide rows, few edges: WPE waves (1, or a whole block) take one edge over the
 // whole row, so the stage is one launch and leaves no partials for a second
 // one.  A lane reads both rows four features at a time, kRowChunks of each in
@@ -2634,6 +2659,7 @@ template <int PREC>
 static void launch_edge_class(const EdgeClass &c, int par, hipStream_t s) {
   const dim3 g(c.nblk), t(kEdgeBlock);
   switch (c.nv) {
+    case 0: hipLaunchKernelGGL((k_edge_items_any<PREC>), g, t, 0, s, c.eargs[par], c.etab); break;
     case 1: hipLaunchKernelGGL((k_edge_items_batch<PREC, 1>), g, t, 0, s, c.eargs[par], c.etab); break;
     case 2: hipLaunchKernelGGL((k_edge_items_batch<PREC, 2>), g, t, 0, s, c.eargs[par], c.etab); break;
     case 4: hipLaunchKernelGGL((k_edge_items_batch<PREC, 4>), g, t, 0, s, c.eargs[par], c.etab); break;
@@ -2710,14 +2736,14 @@ static void free_launch_set(LaunchSet &L) {
 // laid out in the given order of instances: instance k gets tile shape
 // vec_of[k] (64 * vec features per wave) and about ipw_of[k] items per wave
 // (waves with several items prefetch the next); point launches are grouped
-// by (vec, ipw), edge launches by each instance's features per lane.  Sets
-// the problems' tile fields and scalar slot 0.
+// by (vec, ipw), edge launches by each instance's features per lane (one_edge:
+// one launch for all).  Sets the problems' tile fields and scalar slot 0.
 constexpr int kBatchEdgeItems = 4;  // items per wave of the batched item edge sweep
 
 static cc_status build_launch_set(LaunchSet &L, const std::vector<Problem *> &probs,
                                   const std::vector<const BatchInst *> &bis,
                                   const std::vector<int> &order, const std::vector<int> &vec_of,
-                                  const std::vector<int> &ipw_of, int K, hipStream_t st) {
+                                  const std::vector<int> &ipw_of, int K, bool one_edge, hipStream_t st) {
   free_launch_set(L);
   const int n_inst = (int)probs.size();
   std::vector<PointArgs> pa[2];
@@ -2770,11 +2796,13 @@ static cc_status build_launch_set(LaunchSet &L, const std::vector<Problem *> &pr
     CC_TRY(upload(&c.ptab, pt, st));
     L.pcls.push_back(c);
   }
-  for (int nv : {1, 2, 4, 8, 16}) {
+  for (int nv : {0, 1, 2, 4, 8, 16}) {  // 0: every width
+    if ((nv == 0) != one_edge) continue;
     std::vector<int2> et;
     for (int b : order)
-      if (probs[b]->item_nv == nv)
-        for (int q = 0; q < eblocks[b]; ++q) et.push_back(make_int2(b, q));
+      if (one_edge || probs[b]->item_nv == nv)
+        for (int q = 0; q < eblocks[b]; ++q)
+          et.push_back(make_int2(b, one_edge ? probs[b]->item_nv << kNvShift | q : q));
     if (et.empty()) continue;
     EdgeClass c;
     c.nv = nv;
@@ -2793,7 +2821,7 @@ static cc_status batch_configure(Batch *B, const std::vector<int> *order = nullp
   std::vector<const BatchInst *> bis;
   for (size_t b = 0; b < B->probs.size(); ++b) bis.push_back(B->bi + b);
   CC_TRY(build_launch_set(B->ls, B->probs, bis, order ? *order : B->order, B->inst_vec, B->inst_ipw,
-                          B->opts.test_every, B->stream));
+                          B->opts.test_every, false, B->stream));
   if (B->gexec) (void)hipGraphExecDestroy(B->gexec);
   if (B->graph) (void)hipGraphDestroy(B->graph);
   B->gexec = nullptr;
@@ -3371,7 +3399,7 @@ cc_status server_step(Server *S, int32_t *n_active, int32_t *n_waiting, int32_t 
         return probs[a]->n * probs[a]->ld > probs[b]->n * probs[b]->ld;
       });
       CC_TRY(build_launch_set(S->ls, probs, bis, order, std::vector<int>(na, S->vec),
-                              std::vector<int>(na, S->ipw), S->opts.test_every, S->stream));
+                              std::vector<int>(na, S->ipw), S->opts.test_every, true, S->stream));
       CC_HIP(hipMemcpyAsync(S->d_sc0, sc0.data(), sc0.size() * sizeof(DevScalars *), hipMemcpyHostToDevice, S->stream));
       S->dirty = false;
     }
