@@ -157,13 +157,9 @@ cc_status cc_solve_path(cc_problem_t prob, int32_t n_gamma, const double *gammas
   for (int32_t g = 0; g < n_gamma; ++g) {
     cc_solve_info info;
     std::memset(&info, 0, sizeof(info));
-    cc_status s = solve(P, gammas[g], o, &info);
+    cc_status s = solve(P, gammas[g], o, &info, labels ? labels + (size_t)g * P->n : nullptr);
     if (infos) infos[g] = info;
     if (s != CC_OK) return s;
-    if (labels) {
-      s = write_labels(P, labels + (size_t)g * P->n, nullptr);
-      if (s != CC_OK) return s;
-    }
     if (U_path) {
       s = copy_U(P, CC_DTYPE_F32, U_path + (size_t)g * P->n * P->p, P->p);
       if (s != CC_OK) return s;
@@ -194,13 +190,9 @@ cc_status cc_solve_path_pc(cc_problem_t prob, int32_t n_gamma, const double *gam
   for (int32_t g = 0; g < n_gamma; ++g) {
     cc_solve_info info;
     std::memset(&info, 0, sizeof(info));
-    cc_status s = solve(P, gammas[g], o, &info);
+    cc_status s = solve(P, gammas[g], o, &info, labels ? labels + (size_t)g * P->n : nullptr);
     if (infos) infos[g] = info;
     if (s != CC_OK) return s;
-    if (labels) {
-      s = write_labels(P, labels + (size_t)g * P->n, nullptr);
-      if (s != CC_OK) return s;
-    }
     s = project_U(P, r, V, center, proj + (size_t)g * P->n * r);
     if (s != CC_OK) return s;
     o.warm_start = 1;

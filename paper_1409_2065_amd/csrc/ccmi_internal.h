@@ -126,7 +126,9 @@ struct Problem {
   int eslab_tpg = 1;         // feature tiles per block of the slab edge sweep
   int eslab_ntf = 1;         // feature tiles of width edge_f
   int edge_f = 0;            // LDS tile width of the slab edge sweep
-  // device buffers
+  // device buffers, all of them parts of mem but for those made by solves
+  // (trace, H, T, Umiss, moff)
+  void *mem = nullptr;
   void *X = nullptr;         // n x ld, float (f32/mixed) or double (f64)
   uint8_t *M = nullptr;      // n x ld or null
   void *U = nullptr;         // n x ld, state type
@@ -164,6 +166,7 @@ struct Problem {
   DevScalars *sc_host = nullptr; // pinned mirror
   int32_t *flag_host = nullptr;  // pinned
   int32_t *ncl_dev = nullptr;
+  int32_t *lab = nullptr;    // labels nobody asked for (their count is wanted)
   ResidentPlan res;
   int32_t *res_order = nullptr, *res_estart = nullptr;
   unsigned long long *res_prof = nullptr;  // sampled ticks: point phase, edge phase, samples
@@ -276,7 +279,7 @@ cc_status problem_create(int64_t n, int64_t p, int32_t x_dtype, const void *X,
 void problem_free(Problem *P);
 cc_status reset_state(Problem *P);
 cc_status solve(Problem *P, double gamma, const cc_solve_opts &o,
-                cc_solve_info *info);
+                cc_solve_info *info, int32_t *labels = nullptr);
 cc_status write_labels(Problem *P, int32_t *labels, int32_t *ncl_host);
 cc_status copy_U(Problem *P, int32_t out_dtype, void *dst, int64_t ldu);
 cc_status get_fused(Problem *P, uint8_t *fused);
@@ -287,7 +290,7 @@ cc_status profile(Problem *P, int32_t sample_every);
 cc_status harvest_profile(Problem *P);
 cc_status components(int64_t n, int64_t E, const int32_t *ei,
                      const int32_t *ej, const uint8_t *keep, const double *s,
-                     int32_t *labels, int32_t *ncl_dev, hipStream_t stream);
+                     int32_t *labels, int32_t *ncl_dev, hipStream_t stream, int count = 1);
 
 // Served solves: requests queue on the host, are admitted while the HBM
 // budget allows, and share launches with the other admitted requests.
@@ -303,8 +306,10 @@ struct Request {
   Problem *P = nullptr;            // owned once admitted
   int64_t footprint = 0;           // bytes counted against the budget
   bool charged = false;            // footprint counted in the server's used bytes
-  BatchInst *bi = nullptr;         // device descriptor and its arrays
+  void *mem = nullptr;             // device descriptor and its arrays, one allocation
+  BatchInst *bi = nullptr;
   double *gconst = nullptr;
+  int32_t *ncl = nullptr;          // clusters per gamma
   uint8_t *fused = nullptr;
   double *info = nullptr;
   unsigned long long *tdone = nullptr;

@@ -1514,12 +1514,27 @@ __global__ void k_fused_flags(int E, const double *s, uint8_t *out) {
 
 // Connected components of the kept edges (keep[e] != 0, or s[e] == 0 when
 // keep is null), labelled by the smallest vertex index: min-label hooking
-// with pointer jumping, one workgroup, at most n + 2 rounds.
+// with pointer jumping, at most n + 2 rounds.  One workgroup per label
+// problem: block b takes edge flags keep + b E and writes labels lab + b n
+// and the count ncl[b].  A round is a chain of dependent reads of labels, so
+// up to kLabelLds points they live in LDS (LDS = true) and go to memory once
+// at the end; more points keep them in memory.  Both reach the same labels:
+// hooking and jumping only ever lower a label towards the smallest index of
+// its component, and the rounds end when neither can.
+template <bool LDS>
 __global__ __launch_bounds__(1024) void k_components(int n, int E, const int32_t *ei,
                                                      const int32_t *ej, const uint8_t *keep,
-                                                     const double *s, int32_t *lab, int32_t *ncl) {
+                                                     const double *s, int32_t *lab_out,
+                                                     int32_t *ncl) {
+  extern __shared__ int32_t lab_s[];
   __shared__ int changed;
   __shared__ int cnt_s[1024 / kWave];
+  constexpr auto kScope = LDS ? __HIP_MEMORY_SCOPE_WORKGROUP : __HIP_MEMORY_SCOPE_AGENT;
+  if (keep) keep += (size_t)blockIdx.x * E;
+  lab_out += (size_t)blockIdx.x * n;
+  int32_t *lab = LDS ? lab_s : lab_out;
+  auto get = [&](int i) { return __hip_atomic_load(&lab[i], __ATOMIC_RELAXED, kScope); };
+  auto lower = [&](int i, int v) { __hip_atomic_fetch_min(&lab[i], v, __ATOMIC_RELAXED, kScope); };
   for (int i = threadIdx.x; i < n; i += blockDim.x) lab[i] = i;
   __syncthreads();
   for (int round = 0; round < n + 2; ++round) {
@@ -1530,43 +1545,44 @@ __global__ __launch_bounds__(1024) void k_components(int n, int E, const int32_t
       const bool fused = keep ? (keep[e] != 0) : (s[e] == 0.0);
       if (!fused) continue;
       const int a = ei[e], b = ej[e];
-      const int la = __hip_atomic_load(&lab[a], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const int lbv = __hip_atomic_load(&lab[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const int la = get(a), lbv = get(b);
       if (la != lbv) {
         const int lo = min(la, lbv), hi = max(la, lbv);
-        atomicMin(&lab[a], lo);
-        atomicMin(&lab[b], lo);
-        atomicMin(&lab[hi], lo);
+        lower(a, lo);
+        lower(b, lo);
+        lower(hi, lo);
         local = 1;
       }
     }
     if (local) changed = 1;
     __syncthreads();
+    const int ch = changed;
+    if (!ch) break;
     // pointer jumping
     for (int i = threadIdx.x; i < n; i += blockDim.x) {
-      int l = __hip_atomic_load(&lab[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      int ll = __hip_atomic_load(&lab[l], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      int l = get(i);
+      int ll = get(l);
       while (ll < l) {
         l = ll;
-        ll = __hip_atomic_load(&lab[l], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        ll = get(l);
       }
-      atomicMin(&lab[i], l);
+      lower(i, l);
     }
     __syncthreads();
-    const int ch = changed;
-    __syncthreads();
-    if (!ch) break;
   }
   int c = 0;
-  for (int i = threadIdx.x; i < n; i += blockDim.x)
-    c += (__hip_atomic_load(&lab[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == i) ? 1 : 0;
+  for (int i = threadIdx.x; i < n; i += blockDim.x) {
+    const int l = get(i);
+    if (LDS) lab_out[i] = l;
+    c += l == i ? 1 : 0;
+  }
   for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off, kWave);
   if (threadIdx.x % kWave == 0) cnt_s[threadIdx.x / kWave] = c;
   __syncthreads();
   if (threadIdx.x == 0) {
     int tot = 0;
     for (int w = 0; w < (int)(blockDim.x / kWave); ++w) tot += cnt_s[w];
-    *ncl = tot;
+    ncl[blockIdx.x] = tot;
   }
 }
 
@@ -1574,6 +1590,7 @@ __global__ __launch_bounds__(1024) void k_components(int n, int E, const int32_t
 static inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 constexpr int64_t kSlabBytes = 128 * 1024;  // LDS budget of the slab sweeps
+constexpr int64_t kLabelLds = 16000;        // points whose labels fit in the 64 KB any kernel may take
 
 static size_t ts_size(int prec) { return prec == kF32 ? 4 : 8; }
 static size_t tx_size(int prec) { return prec == kF64 ? 8 : 4; }
@@ -1920,22 +1937,35 @@ cc_status harvest_profile(Problem *P) {
   return CC_OK;
 }
 
+// Arrays cut from one device allocation, each 256-byte aligned; those given
+// as host vectors (from) are copied there together, from stage().
+struct Carve {
+  struct Part { void **slot; size_t at; const void *src; size_t len; };
+  std::vector<Part> parts;
+  size_t bytes = 0;
+  template <typename T> void add(T **slot, size_t len, const void *src = nullptr) {
+    parts.push_back({(void **)slot, bytes, src, len});
+    bytes += (std::max<size_t>(len, 8) + 255) / 256 * 256;
+  }
+  template <typename T> void from(T **slot, const std::vector<T> &v) { add(slot, v.size() * sizeof(T), v.data()); }
+  void place(char *base) const {
+    for (const Part &q : parts) *q.slot = base + q.at;
+  }
+  std::vector<char> stage() const {
+    std::vector<char> h(bytes, 0);
+    for (const Part &q : parts)
+      if (q.src && q.len) std::memcpy(h.data() + q.at, q.src, q.len);
+    return h;
+  }
+};
+
 void problem_free(Problem *P) {
   if (!P) return;
-  void *bufs[] = {P->X, P->M, P->U, P->A[0], P->A[1], P->Usnap, P->Asnap, P->rowptr, P->col, P->eid, P->uptr,
-                  P->itemI, P->itemJ, P->itemE,
-                  P->ei, P->ej, P->w, P->s, P->nb[0], P->nb[1], P->qe, P->qE, P->epos, P->degE, P->colE,
-                  P->eidE, P->part, P->psum,
-                  P->esum, P->trace, P->sc, P->ncl_dev, P->res_order, P->res_estart, P->res_prof, P->slab_order, P->H, P->T[0], P->T[1], P->Umiss, P->moff};
+  void *bufs[] = {P->mem, P->trace, P->H, P->T[0], P->T[1], P->Umiss, P->moff};
   for (void *b : bufs)
     if (b) (void)hipFree(b);
-  if (Traits<kMixed>::mirror && P->precision == kMixed) {
-    if (P->G[0]) (void)hipFree(P->G[0]);
-    if (P->G[1]) (void)hipFree(P->G[1]);
-  }
   for (hipEvent_t ev : P->prof_events) (void)hipEventDestroy(ev);
-  if (P->sc_host) (void)hipHostFree(P->sc_host);
-  if (P->flag_host) (void)hipHostFree(P->flag_host);
+  if (P->sc_host) (void)hipHostFree(P->sc_host);  // flag_host lies behind it
   delete P;
 }
 
@@ -2029,7 +2059,7 @@ static void choose_tiles(Problem *P) {
   }
 }
 
-cc_status reset_state(Problem *P);
+static cc_status enqueue_reset(Problem *P);
 
 cc_status problem_create(int64_t n, int64_t p, int32_t x_dtype, const void *X,
                          int64_t ldx, const uint8_t *mask, int64_t ldm,
@@ -2058,7 +2088,7 @@ cc_status problem_create(int64_t n, int64_t p, int32_t x_dtype, const void *X,
     CC_HIP(hipMemcpyAsync(hw.data(), w, n_edges * 8, hipMemcpyDeviceToHost, stream));
     CC_HIP(hipStreamSynchronize(stream));
   }
-  std::vector<int64_t> keys(n_edges);
+  bool sorted = true;  // by (ei, ej), strictly: then no edge is there twice
   for (int64_t e = 0; e < n_edges; ++e) {
     if (hi[e] < 0 || hj[e] >= n || hi[e] >= hj[e]) {
       set_error("edge " + std::to_string(e) + " invalid: need 0 <= ei < ej < n");
@@ -2068,10 +2098,11 @@ cc_status problem_create(int64_t n, int64_t p, int32_t x_dtype, const void *X,
       set_error("weight " + std::to_string(e) + " must be finite and > 0");
       return CC_ERR_INVALID_ARG;
     }
-    keys[e] = (int64_t)hi[e] * n + hj[e];
+    if (e > 0 && (hi[e] < hi[e - 1] || (hi[e] == hi[e - 1] && hj[e] <= hj[e - 1]))) sorted = false;
   }
-  {
-    std::vector<int64_t> sk(keys);
+  if (!sorted) {
+    std::vector<int64_t> sk(n_edges);
+    for (int64_t e = 0; e < n_edges; ++e) sk[e] = (int64_t)hi[e] * n + hj[e];
     std::sort(sk.begin(), sk.end());
     for (size_t k = 1; k < sk.size(); ++k)
       if (sk[k] == sk[k - 1]) { set_error("duplicate edge"); return CC_ERR_INVALID_ARG; }
@@ -2090,40 +2121,7 @@ cc_status problem_create(int64_t n, int64_t p, int32_t x_dtype, const void *X,
   struct Guard { Problem *&P; bool ok = false; ~Guard() { if (!ok) problem_free(P); } } guard{P};
 
   const size_t nl = (size_t)n * P->ld;
-  CC_TRY(dmalloc(&P->X, nl * tx_size(precision)));
-  if (mask) CC_TRY(dmalloc((void **)&P->M, nl));
-  CC_TRY(dmalloc(&P->U, nl * ts_size(precision)));
-  CC_TRY(dmalloc(&P->A[0], nl * ta_size(precision)));
-  CC_TRY(dmalloc(&P->A[1], nl * ta_size(precision)));
-  CC_TRY(dmalloc(&P->Usnap, nl * ts_size(precision)));
-  CC_TRY(dmalloc(&P->Asnap, nl * ts_size(precision)));
-  if (precision == kMixed) {
-    CC_TRY(dmalloc(&P->G[0], nl * tg_size(precision)));
-    CC_TRY(dmalloc(&P->G[1], nl * tg_size(precision)));
-  } else {
-    P->G[0] = P->A[0]; P->G[1] = P->A[1];
-  }
   const int64_t E = n_edges;
-  CC_TRY(dmalloc((void **)&P->rowptr, (n + 1) * 4));
-  CC_TRY(dmalloc((void **)&P->uptr, n * 4));
-  CC_TRY(dmalloc((void **)&P->col, 2 * E * 4));
-  CC_TRY(dmalloc((void **)&P->eid, 2 * E * 4));
-  CC_TRY(dmalloc((void **)&P->ei, E * 4));
-  CC_TRY(dmalloc((void **)&P->ej, E * 4));
-  CC_TRY(dmalloc((void **)&P->w, E * 8));
-  CC_TRY(dmalloc((void **)&P->s, E * 8));
-  CC_TRY(dmalloc((void **)&P->nb[0], E * 8));
-  CC_TRY(dmalloc((void **)&P->nb[1], E * 8));
-  CC_TRY(dmalloc((void **)&P->qe, E * 8));
-  CC_TRY(dmalloc((void **)&P->epos, 2 * E * 4));
-  CC_TRY(dmalloc((void **)&P->part, E * (P->efused || P->erows ? 1 : P->entile) * 8));
-  // one row of point partials per block of the point sweep
-  CC_TRY(dmalloc((void **)&P->psum, kMaxBlocks * 8 * 8));
-  CC_TRY(dmalloc((void **)&P->esum, (size_t)kEsumRows * kEsumStride * 8));
-  CC_TRY(dmalloc((void **)&P->sc, 2 * sizeof(DevScalars)));
-  CC_TRY(dmalloc((void **)&P->ncl_dev, 4));
-  CC_HIP(hipHostMalloc((void **)&P->sc_host, sizeof(DevScalars), hipHostMallocDefault));
-  CC_HIP(hipHostMalloc((void **)&P->flag_host, 64, hipHostMallocDefault));
 
   // ---- symmetric CSR with sorted columns ----
   std::vector<int32_t> deg(n + 1, 0);
@@ -2141,7 +2139,8 @@ cc_status problem_create(int64_t n, int64_t p, int32_t x_dtype, const void *X,
   std::vector<int32_t> hcol(2 * E), heid(2 * E), hup(n), hpos(2 * E);
   int64_t maxdeg = 0;
   for (int64_t i = 0; i < n; ++i) {
-    std::sort(ent.begin() + rp[i], ent.begin() + rp[i + 1]);
+    // sorted edges leave every row in order: lower ends first, each run ascending
+    if (!sorted) std::sort(ent.begin() + rp[i], ent.begin() + rp[i + 1]);
     int32_t up = rp[i + 1];
     for (int32_t k = rp[i]; k < rp[i + 1]; ++k) {
       hcol[k] = ent[k].first; heid[k] = ent[k].second;
@@ -2155,8 +2154,8 @@ cc_status problem_create(int64_t n, int64_t p, int32_t x_dtype, const void *X,
   P->max_deg = maxdeg;
   // edge work items: the upper neighbours of each point in runs of up to
   // kItemEdges (unused slots -1)
+  std::vector<int32_t> iI, iJ, iE;
   {
-    std::vector<int32_t> iI, iJ, iE;
     for (int64_t i = 0; i < n; ++i) {
       for (int32_t k = hup[i]; k < rp[i + 1]; k += kItemEdges) {
         iI.push_back((int32_t)i);
@@ -2172,33 +2171,14 @@ cc_status problem_create(int64_t n, int64_t p, int32_t x_dtype, const void *X,
       const char *es = getenv("CCMI_EDGE_SLAB_ITEMS");
       P->eslab_items = P->n_items <= (int64_t)kSlabItemSlots * 1024 && !(es && atoi(es) == 0);
     }
-    CC_TRY(dmalloc((void **)&P->itemI, iI.size() * 4));
-    CC_TRY(dmalloc((void **)&P->itemJ, iJ.size() * 4));
-    CC_TRY(dmalloc((void **)&P->itemE, iE.size() * 4));
-    if (!iI.empty()) {
-      CC_HIP(hipMemcpyAsync(P->itemI, iI.data(), iI.size() * 4, hipMemcpyHostToDevice, stream));
-      CC_HIP(hipMemcpyAsync(P->itemJ, iJ.data(), iJ.size() * 4, hipMemcpyHostToDevice, stream));
-      CC_HIP(hipMemcpyAsync(P->itemE, iE.data(), iE.size() * 4, hipMemcpyHostToDevice, stream));
-      CC_HIP(hipStreamSynchronize(stream));  // the host vectors go out of scope
-    }
   }
   P->nbe = edge_rows(P);
-  if (slab_plan(n, P->ld, deg.data(), precision, &P->slab)) {
-    const size_t bytes = P->slab.order.size() * 4;
-    CC_TRY(dmalloc((void **)&P->slab_order, bytes));
-    CC_HIP(hipMemcpyAsync(P->slab_order, P->slab.order.data(), bytes, hipMemcpyHostToDevice, stream));
-  }
-  if (!P->slab.forced && resident_plan(n, P->ld, E, deg.data(), precision, &P->res)) {
-    CC_TRY(dmalloc((void **)&P->res_order, n * 4));
-    CC_TRY(dmalloc((void **)&P->res_estart, n * 4));
-    CC_TRY(dmalloc((void **)&P->res_prof, 3 * 8));
-    CC_HIP(hipMemcpyAsync(P->res_order, P->res.order.data(), n * 4, hipMemcpyHostToDevice, stream));
-    CC_HIP(hipMemcpyAsync(P->res_estart, P->res.estart.data(), n * 4, hipMemcpyHostToDevice, stream));
-    CC_HIP(hipMemsetAsync(P->res_prof, 0, 3 * 8, stream));
-  }
+  const bool slab = slab_plan(n, P->ld, deg.data(), precision, &P->slab);
+  const bool resident =
+      !P->slab.forced && resident_plan(n, P->ld, E, deg.data(), precision, &P->res);
   // ELL copy of the neighbour lists for the point sweep
-  // (the stride a multiple of 4: the slab sweep reads four entries at a time)
-  const int64_t S = (std::max<int64_t>(maxdeg, 1) + 3) / 4 * 4;
+  // (the stride a multiple of 4 for the slab sweep, which reads four entries at a time)
+  const int64_t d1 = std::max<int64_t>(maxdeg, 1), S = slab ? (d1 + 3) / 4 * 4 : d1;
   // the sweeps index ELL slots (n * S of them) in 32 bits: checked before
   // any of the n * S host or device arrays exists
   if (n * S > ((int64_t)1 << 31) - 1) {
@@ -2223,45 +2203,67 @@ cc_status problem_create(int64_t n, int64_t p, int32_t x_dtype, const void *X,
     const int64_t row = (e2 % 2 == 0) ? hi[e2 / 2] : hj[e2 / 2];
     hposE[e2] = (int32_t)ell_slot(row, k - rp[row]);
   }
-  CC_TRY(dmalloc((void **)&P->degE, n * 4));
-  CC_TRY(dmalloc((void **)&P->colE, n * S * 4));
-  CC_TRY(dmalloc((void **)&P->eidE, n * S * 4));
-  CC_TRY(dmalloc((void **)&P->qE, n * S * 8));
-  CC_HIP(hipMemcpyAsync(P->degE, hdegE.data(), n * 4, hipMemcpyHostToDevice, stream));
-  CC_HIP(hipMemcpyAsync(P->colE, hcolE.data(), n * S * 4, hipMemcpyHostToDevice, stream));
-  CC_HIP(hipMemcpyAsync(P->eidE, heidE.data(), n * S * 4, hipMemcpyHostToDevice, stream));
-  CC_HIP(hipMemcpyAsync(P->rowptr, rp.data(), (n + 1) * 4, hipMemcpyHostToDevice, stream));
-  CC_HIP(hipMemcpyAsync(P->uptr, hup.data(), n * 4, hipMemcpyHostToDevice, stream));
-  if (E > 0) {
-    CC_HIP(hipMemcpyAsync(P->col, hcol.data(), 2 * E * 4, hipMemcpyHostToDevice, stream));
-    CC_HIP(hipMemcpyAsync(P->eid, heid.data(), 2 * E * 4, hipMemcpyHostToDevice, stream));
-    CC_HIP(hipMemcpyAsync(P->epos, hposE.data(), 2 * E * 4, hipMemcpyHostToDevice, stream));
-    CC_HIP(hipMemcpyAsync(P->ei, hi.data(), E * 4, hipMemcpyHostToDevice, stream));
-    CC_HIP(hipMemcpyAsync(P->ej, hj.data(), E * 4, hipMemcpyHostToDevice, stream));
-    CC_HIP(hipMemcpyAsync(P->w, hw.data(), E * 8, hipMemcpyHostToDevice, stream));
+  // ---- device memory: one allocation, what is uploaded at its front ----
+  // (an allocation costs the host about 10 us, a release 20, a copy 14)
+  Carve up, mem;
+  up.from(&P->colE, hcolE); up.from(&P->eidE, heidE); up.from(&P->degE, hdegE);
+  up.from(&P->rowptr, rp); up.from(&P->uptr, hup);
+  up.from(&P->col, hcol); up.from(&P->eid, heid); up.from(&P->epos, hposE);
+  up.from(&P->ei, hi); up.from(&P->ej, hj); up.from(&P->w, hw);
+  up.from(&P->itemI, iI); up.from(&P->itemJ, iJ); up.from(&P->itemE, iE);
+  if (slab) up.from(&P->slab_order, P->slab.order);
+  if (resident) {
+    up.from(&P->res_order, P->res.order);
+    up.from(&P->res_estart, P->res.estart);
   }
+  double *mean = nullptr, *dev2 = nullptr;  // dev2: p values, then the non-finite flag
+  mem.add(&P->X, nl * tx_size(precision));
+  if (mask) mem.add(&P->M, nl);
+  mem.add(&P->U, nl * ts_size(precision));
+  for (int q = 0; q < 2; ++q) mem.add(&P->A[q], nl * ta_size(precision));
+  mem.add(&P->Usnap, nl * ts_size(precision));
+  mem.add(&P->Asnap, nl * ts_size(precision));
+  if (precision == kMixed)
+    for (int q = 0; q < 2; ++q) mem.add(&P->G[q], nl * tg_size(precision));
+  mem.add(&P->s, E * 8);
+  for (int q = 0; q < 2; ++q) mem.add(&P->nb[q], E * 8);
+  mem.add(&P->qe, E * 8);
+  mem.add(&P->qE, n * S * 8);
+  mem.add(&P->part, E * (P->efused || P->erows ? 1 : P->entile) * 8);
+  mem.add(&P->psum, kMaxBlocks * 8 * 8);  // one row of point partials per block of the point sweep
+  mem.add(&P->esum, (size_t)kEsumRows * kEsumStride * 8);
+  mem.add(&P->sc, 2 * sizeof(DevScalars));
+  mem.add(&P->ncl_dev, 4);
+  mem.add(&P->lab, n * 4);
+  mem.add(&P->res_prof, 3 * 8);
+  mem.add(&mean, p * 8);
+  mem.add(&dev2, (p + 1) * 8);
+  CC_TRY(dmalloc(&P->mem, up.bytes + mem.bytes));
+  up.place((char *)P->mem);
+  mem.place((char *)P->mem + up.bytes);
+  if (precision != kMixed) { P->G[0] = P->A[0]; P->G[1] = P->A[1]; }
+  const std::vector<char> stage = up.stage();
+  CC_HIP(hipMemcpyAsync(P->mem, stage.data(), stage.size(), hipMemcpyHostToDevice, stream));
+  CC_HIP(hipMemsetAsync(P->res_prof, 0, 3 * 8, stream));
+  constexpr size_t kScBytes = (sizeof(DevScalars) + 63) / 64 * 64;
+  CC_HIP(hipHostMalloc((void **)&P->sc_host, kScBytes + 64, hipHostMallocDefault));
+  P->flag_host = (int32_t *)((char *)P->sc_host + kScBytes);
   double w2 = 0.0;
   for (int64_t e = 0; e < E; ++e) w2 += hw[e] * hw[e];
   P->w2 = w2;
 
   // ---- column statistics and the initial state ----
-  double *mean = nullptr, *dev2 = nullptr;
-  int *bad = nullptr;
-  CC_TRY(dmalloc((void **)&mean, p * 8));
-  struct Tmp { void *a, *b, *c; ~Tmp() { if (a) (void)hipFree(a); if (b) (void)hipFree(b); if (c) (void)hipFree(c); } } tmp{mean, nullptr, nullptr};
-  CC_TRY(dmalloc((void **)&dev2, p * 8));
-  tmp.b = dev2;
-  CC_TRY(dmalloc((void **)&bad, 4));
-  tmp.c = bad;
-  CC_HIP(hipMemsetAsync(bad, 0, 4, stream));
+  int *bad = (int *)(dev2 + p);
+  CC_HIP(hipMemsetAsync(bad, 0, 8, stream));
   column_moments(n, p, x_dtype, X, ldx, mask, ldm, true, mean, dev2, false, bad, stream);
   CC_HIP(hipGetLastError());
-  std::vector<double> hdev2(p);
-  int hbad = 0;
-  CC_HIP(hipMemcpyAsync(hdev2.data(), dev2, p * 8, hipMemcpyDeviceToHost, stream));
-  CC_HIP(hipMemcpyAsync(&hbad, bad, 4, hipMemcpyDeviceToHost, stream));
+  std::vector<double> hdev2(p + 1);
+  CC_HIP(hipMemcpyAsync(hdev2.data(), dev2, (p + 1) * 8, hipMemcpyDeviceToHost, stream));
   CC_HIP(hipStreamSynchronize(stream));
+  int hbad = 0;
+  std::memcpy(&hbad, &hdev2[p], 4);
   if (hbad) { set_error("observed X has non-finite entries"); return CC_ERR_INVALID_ARG; }
+  hdev2.pop_back();
   P->dev2 = std::accumulate(hdev2.begin(), hdev2.end(), 0.0);
 
   const int ib = (int)cdiv(nl, 256);
@@ -2280,7 +2282,6 @@ cc_status problem_create(int64_t n, int64_t p, int32_t x_dtype, const void *X,
   }
 #undef CC_INIT
   CC_HIP(hipGetLastError());
-  CC_HIP(hipStreamSynchronize(stream));
   CC_TRY(reset_state(P));
   guard.ok = true;
   *out = P;
@@ -2288,7 +2289,7 @@ cc_status problem_create(int64_t n, int64_t p, int32_t x_dtype, const void *X,
 }
 
 // Back to the initial state U = A' = X-tilde, s = 1 (stored in buffer 0).
-cc_status reset_state(Problem *P) {
+static cc_status enqueue_reset(Problem *P) {
   const size_t nl = (size_t)P->n * P->ld;
   const size_t bytes = nl * ts_size(P->precision);
   // U and A[0] are rebuilt from the stored X-tilde copy
@@ -2316,8 +2317,13 @@ cc_status reset_state(Problem *P) {
   CC_HIP(hipGetLastError());
   launch_edge_init(P);
   CC_HIP(hipGetLastError());
-  CC_HIP(hipStreamSynchronize(P->stream));
   P->state_valid = true;
+  return CC_OK;
+}
+
+cc_status reset_state(Problem *P) {
+  CC_TRY(enqueue_reset(P));
+  CC_HIP(hipStreamSynchronize(P->stream));
   return CC_OK;
 }
 
@@ -2392,7 +2398,12 @@ static cc_status harvest_resident(Problem *P) {
   return CC_OK;
 }
 
-cc_status solve(Problem *P, double gamma, const cc_solve_opts &o, cc_solve_info *info) {
+// labels: where the labels of the final state go (null: scratch, when info
+// asks for their count).  The host waits twice per solve: for the scalars
+// that end it, and for the count.  A resident block has nearly always ended
+// by its first return, so its labels are enqueued behind it and both are
+// waited for together.
+cc_status solve(Problem *P, double gamma, const cc_solve_opts &o, cc_solve_info *info, int32_t *labels) {
   if (!(gamma >= 0.0) || !std::isfinite(gamma)) { set_error("gamma must be finite and >= 0"); return CC_ERR_INVALID_ARG; }
   if (o.max_iter < 1) { set_error("max_iter must be >= 1"); return CC_ERR_INVALID_ARG; }
   if (o.test_every < 1) { set_error("test_every must be >= 1"); return CC_ERR_INVALID_ARG; }
@@ -2429,7 +2440,7 @@ cc_status solve(Problem *P, double gamma, const cc_solve_opts &o, cc_solve_info 
     if (build_miss_index(P) != CC_OK) P->lazy_u = false;  // store U every iteration
   }
   const auto t0 = std::chrono::steady_clock::now();
-  if (!o.warm_start || !P->state_valid) CC_TRY(reset_state(P));
+  if (!o.warm_start || !P->state_valid) CC_TRY(enqueue_reset(P));
   double rho, eps, thr;
   solve_constants(P, gamma, o, &rho, &eps, &thr);
   P->cur_K = o.test_every;
@@ -2455,6 +2466,13 @@ cc_status solve(Problem *P, double gamma, const cc_solve_opts &o, cc_solve_info 
   // sweeps m = 0 .. max_iter, each finished by the next launch pair; the
   // last pair only finishes (the stop rule ends the solve by then)
   const int64_t last = (int64_t)o.max_iter + 1;
+  int32_t *lab = labels ? labels : P->lab;
+  auto enqueue_labels = [&]() -> cc_status {
+    if (!info) return CC_OK;
+    CC_TRY(components(P->n, P->E, P->ei, P->ej, nullptr, P->s, lab, P->ncl_dev, P->stream));
+    CC_HIP(hipMemcpyAsync(P->flag_host, P->ncl_dev, 4, hipMemcpyDeviceToHost, P->stream));
+    return CC_OK;
+  };
   // a resident block ends at the stop rule by itself: it is handed many
   // iterations at a time (kResidentSweeps of a few microseconds each)
   if (resident) {
@@ -2463,9 +2481,9 @@ cc_status solve(Problem *P, double gamma, const cc_solve_opts &o, cc_solve_info 
       const int iters = (int)std::min<int64_t>(chunk, last + 1 - it);
       CC_TRY(resident_run(P, iters));
       P->prof_iter += iters;
-      CC_HIP(hipMemcpyAsync(P->flag_host, &P->sc[P->slot].done, 4, hipMemcpyDeviceToHost, P->stream));
-      CC_HIP(hipStreamSynchronize(P->stream));
-      if (P->flag_host[0]) break;
+      CC_TRY(enqueue_labels());
+      CC_TRY(read_scalars(P));
+      if (P->sc_host->done) break;
     }
     if (P->prof_every > 0) CC_TRY(harvest_resident(P));
   }
@@ -2473,17 +2491,15 @@ cc_status solve(Problem *P, double gamma, const cc_solve_opts &o, cc_solve_info 
     launch_iteration(P);
     if ((it + 1) % check == 0 || it == last) {
       CC_HIP(hipGetLastError());
-      CC_HIP(hipMemcpyAsync(P->flag_host, &P->sc[P->slot].done, 4, hipMemcpyDeviceToHost, P->stream));
-      CC_HIP(hipStreamSynchronize(P->stream));
+      CC_TRY(read_scalars(P));
       if (P->prof_used) harvest_profile(P);
-      if (P->flag_host[0]) break;
+      if (P->sc_host->done) break;
     }
   }
   if (P->lazy_u) {
     launch_u_finish(P);
     CC_HIP(hipGetLastError());
   }
-  CC_TRY(read_scalars(P));
   const DevScalars &h = *P->sc_host;
   P->trace_count = record ? h.iters : 0;
   cc_status st = h.status == 0 ? CC_OK : (cc_status)h.status;
@@ -2504,14 +2520,11 @@ cc_status solve(Problem *P, double gamma, const cc_solve_opts &o, cc_solve_info 
     info->eps = eps;
     info->n_clusters = 0;
     if (st == CC_OK) {
-      int32_t ncl = 0;
-      // labels of the final state into scratch space reused from part
-      int32_t *lab = nullptr;
-      CC_TRY(dmalloc((void **)&lab, P->n * 4));
-      cc_status ls = write_labels(P, lab, &ncl);
-      (void)hipFree(lab);
-      if (ls != CC_OK) return ls;
-      info->n_clusters = ncl;
+      if (!resident) {
+        CC_TRY(enqueue_labels());
+        CC_HIP(hipStreamSynchronize(P->stream));
+      }
+      info->n_clusters = P->flag_host[0];
     }
     info->seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
   }
@@ -2520,9 +2533,13 @@ cc_status solve(Problem *P, double gamma, const cc_solve_opts &o, cc_solve_info 
 
 cc_status components(int64_t n, int64_t E, const int32_t *ei, const int32_t *ej,
                      const uint8_t *keep, const double *s, int32_t *labels,
-                     int32_t *ncl_dev, hipStream_t stream) {
-  hipLaunchKernelGGL(k_components, dim3(1), dim3(1024), 0, stream, (int)n, (int)E, ei, ej, keep,
-                     s, labels, ncl_dev);
+                     int32_t *ncl_dev, hipStream_t stream, int count) {
+  if (n <= kLabelLds)
+    hipLaunchKernelGGL((k_components<true>), dim3(count), dim3(1024), n * 4, stream, (int)n, (int)E,
+                       ei, ej, keep, s, labels, ncl_dev);
+  else
+    hipLaunchKernelGGL((k_components<false>), dim3(count), dim3(1024), 0, stream, (int)n, (int)E,
+                       ei, ej, keep, s, labels, ncl_dev);
   CC_HIP(hipGetLastError());
   return CC_OK;
 }
@@ -3130,17 +3147,15 @@ cc_status batch_run(Batch *B, int32_t *labels, cc_solve_info *infos, double *lat
   hipLaunchKernelGGL(k_batch_done_ticks, dim3((int)cdiv(n_inst, 256)), dim3(256), 0, B->stream, n_inst,
                      (const BatchInst *)B->bi, B->ticks + 1);
   CC_HIP(hipMemcpyAsync(ticks.data(), B->ticks, ticks.size() * 8, hipMemcpyDeviceToHost, B->stream));
-  // labels of every (instance, gamma) from its recorded fusion flags
+  // labels of every (instance, gamma) from its recorded fusion flags: a block
+  // per gamma, a launch per instance
   int64_t loff = 0;
-  for (int b = 0; b < n_inst; ++b) {
+  for (int b = 0; labels && b < n_inst; ++b) {
     Problem *P = B->probs[b];
-    for (int k = 0; k < B->n_gamma[b]; ++k) {
-      const int64_t gk = B->goff[b] + k;
-      if (labels)
-        CC_TRY(components(P->n, P->E, P->ei, P->ej, B->fused + B->foff[b] + (int64_t)k * P->E, nullptr,
-                          labels + loff, B->ncl + gk, B->stream));
-      loff += P->n;
-    }
+    if (B->n_gamma[b] > 0)
+      CC_TRY(components(P->n, P->E, P->ei, P->ej, B->fused + B->foff[b], nullptr, labels + loff,
+                        B->ncl + B->goff[b], B->stream, B->n_gamma[b]));
+    loff += P->n * B->n_gamma[b];
   }
   std::vector<int32_t> hncl(B->total_gamma, 0);
   if (labels) CC_HIP(hipMemcpyAsync(hncl.data(), B->ncl, hncl.size() * 4, hipMemcpyDeviceToHost, B->stream));
@@ -3289,14 +3304,8 @@ cc_status server_submit(Server *S, int64_t n, int64_t p, const float *X, const u
 static void free_request_device(Request *R) {
   if (R->P) problem_free(R->P);
   R->P = nullptr;
-  void *bufs[] = {R->bi, R->gconst, R->fused, R->info, R->tdone};
-  for (void *b : bufs)
-    if (b) (void)hipFree(b);
-  R->bi = nullptr;
-  R->gconst = nullptr;
-  R->fused = nullptr;
-  R->info = nullptr;
-  R->tdone = nullptr;
+  if (R->mem) (void)hipFree(R->mem);
+  R->mem = nullptr;
 }
 
 // Weights, problem and device descriptor of a request; its host copies go.
@@ -3306,25 +3315,19 @@ static cc_status admit(Server *S, Request *R) {
   uint8_t *dM = nullptr;
   int32_t *ei = nullptr, *ej = nullptr;
   double *w = nullptr;
-  struct Tmp {
-    void *b[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
-    ~Tmp() { for (void *x : b) if (x) (void)hipFree(x); }
-  } tmp;
-  CC_TRY(dmalloc((void **)&dX, n * p * 4));
-  tmp.b[0] = dX;
-  CC_HIP(hipMemcpyAsync(dX, R->X.data(), n * p * 4, hipMemcpyHostToDevice, S->stream));
-  if (!R->mask.empty()) {
-    CC_TRY(dmalloc((void **)&dM, n * p));
-    tmp.b[1] = dM;
-    CC_HIP(hipMemcpyAsync(dM, R->mask.data(), n * p, hipMemcpyHostToDevice, S->stream));
-  }
   const int64_t cap = n * R->k;
-  CC_TRY(dmalloc((void **)&ei, cap * 4));
-  tmp.b[2] = ei;
-  CC_TRY(dmalloc((void **)&ej, cap * 4));
-  tmp.b[3] = ej;
-  CC_TRY(dmalloc((void **)&w, cap * 8));
-  tmp.b[4] = w;
+  Carve in;
+  in.add(&dX, n * p * 4);
+  if (!R->mask.empty()) in.add(&dM, n * p);
+  in.add(&ei, cap * 4);
+  in.add(&ej, cap * 4);
+  in.add(&w, cap * 8);
+  void *tmp = nullptr;
+  struct Tmp { void *&b; ~Tmp() { if (b) (void)hipFree(b); } } guard{tmp};
+  CC_TRY(dmalloc(&tmp, in.bytes));
+  in.place((char *)tmp);
+  CC_HIP(hipMemcpyAsync(dX, R->X.data(), n * p * 4, hipMemcpyHostToDevice, S->stream));
+  if (dM) CC_HIP(hipMemcpyAsync(dM, R->mask.data(), n * p, hipMemcpyHostToDevice, S->stream));
   int64_t E = 0;
   double phi_used = 0.0;
   CC_TRY(build_knn_weights(n, p, CC_DTYPE_F32, dX, p, dM, p, R->k, R->phi, 0, ei, ej, w, cap, &E,
@@ -3338,13 +3341,19 @@ static cc_status admit(Server *S, Request *R) {
   for (int g = 0; g < ng; ++g) solve_constants(P, R->gammas[g], S->opts, &R->rho[g], &R->eps[g], &R->thr[g]);
   std::vector<double> gc;
   for (const auto *v : {&R->gammas, &R->rho, &R->eps, &R->thr}) gc.insert(gc.end(), v->begin(), v->end());
-  CC_TRY(upload(&R->gconst, gc, S->stream));
-  CC_TRY(dmalloc((void **)&R->fused, std::max<int64_t>((int64_t)ng * P->E, 1)));
-  CC_TRY(dmalloc((void **)&R->info, (size_t)ng * kInfoVals * 8));
-  CC_TRY(dmalloc((void **)&R->tdone, 8));
+  Carve out;
+  out.add(&R->gconst, gc.size() * 8);
+  out.add(&R->bi, sizeof(BatchInst));
+  out.add(&R->fused, (size_t)ng * P->E);
+  out.add(&R->info, (size_t)ng * kInfoVals * 8);
+  out.add(&R->tdone, 8);
+  out.add(&R->ncl, (size_t)ng * 4);
+  CC_TRY(dmalloc(&R->mem, out.bytes));
+  out.place((char *)R->mem);
   const BatchInst bi{ng, (int)P->E, P->sc, R->gconst, R->gconst + ng, R->gconst + 2 * ng, R->gconst + 3 * ng,
                      P->s, R->fused, R->info, R->tdone, S->n_finished};
-  CC_TRY(upload(&R->bi, std::vector<BatchInst>{bi}, S->stream));
+  CC_HIP(hipMemcpyAsync(R->gconst, gc.data(), gc.size() * 8, hipMemcpyHostToDevice, S->stream));
+  CC_HIP(hipMemcpyAsync(R->bi, &bi, sizeof(bi), hipMemcpyHostToDevice, S->stream));
   hipLaunchKernelGGL(k_inst_init, dim3(1), dim3(1), 0, S->stream, (const BatchInst *)R->bi, S->opts.max_iter,
                      S->opts.test_every);
   CC_HIP(hipGetLastError());
@@ -3447,24 +3456,23 @@ cc_status server_result(Server *S, Request *R, int32_t *labels, cc_solve_info *i
   if (R->state != CC_REQ_DONE) { set_error("request not done"); return CC_ERR_STATE; }
   Problem *P = R->P;
   const int ng = (int)R->gammas.size();
-  int32_t *scratch = nullptr;
-  struct Tmp { int32_t *&p; ~Tmp() { if (p) (void)hipFree(p); } } tmp{scratch};
-  if (!labels && infos) CC_TRY(dmalloc((void **)&scratch, P->n * 4));
+  // a block per gamma; the counts come back with one copy
+  std::vector<int32_t> ncl(ng, 0);
+  if (labels || infos) {
+    int32_t *tmp = nullptr;  // labels that nobody asked for
+    struct Tmp { int32_t *&p; ~Tmp() { if (p) (void)hipFree(p); } } guard{tmp};
+    if (!labels) CC_TRY(dmalloc((void **)&tmp, (size_t)ng * P->n * 4));
+    CC_TRY(components(P->n, P->E, P->ei, P->ej, R->fused, nullptr, labels ? labels : tmp, R->ncl, S->stream, ng));
+    CC_HIP(hipMemcpyAsync(ncl.data(), R->ncl, ng * 4, hipMemcpyDeviceToHost, S->stream));
+    CC_HIP(hipStreamSynchronize(S->stream));
+  }
   for (int g = 0; g < ng; ++g) {
-    int32_t ncl = 0;
-    if (labels || infos) {
-      CC_TRY(components(P->n, P->E, P->ei, P->ej, R->fused + (int64_t)g * P->E, nullptr,
-                        labels ? labels + (int64_t)g * P->n : scratch, P->ncl_dev, S->stream));
-      CC_HIP(hipMemcpyAsync(P->flag_host, P->ncl_dev, 4, hipMemcpyDeviceToHost, S->stream));
-      CC_HIP(hipStreamSynchronize(S->stream));
-      ncl = P->flag_host[0];
-    }
     if (infos) {
       const double *v = &R->hinfo[(size_t)g * kInfoVals];
       cc_solve_info &in = infos[g];
       in.iters = (int32_t)v[0];
       in.converged = (int32_t)v[1];
-      in.n_clusters = ncl;
+      in.n_clusters = ncl[g];
       in.status = (int32_t)v[2];
       in.gamma = R->gammas[g];
       in.objective = v[3];
