@@ -189,11 +189,11 @@ struct Problem {
 struct PointArgs;  // kernel argument blocks (solver.hip)
 struct EdgeArgs;
 
-// Launch tables of problems that share launches: one point-sweep launch per
-// class of (features per lane, items per wave) and one item edge-sweep
-// launch per features-per-lane class of the edge sweep; block -> (instance,
-// local block) tables and per-instance argument blocks for both scalar-slot
-// parities.  The classes cover disjoint instances.
+// Launch tables of problems that share launches: a point-sweep and an item
+// edge-sweep launch per class of (features per lane and items per wave of the
+// point sweep, features per lane of the edge sweep), or one edge launch for
+// all; block -> (instance, local block) tables and per-instance argument
+// blocks for both scalar-slot parities.  The classes cover disjoint instances.
 struct PointClass {
   int vec = 4, ipw = 1, nblk = 0;
   PointArgs *pargs[2] = {nullptr, nullptr};
@@ -227,8 +227,8 @@ struct Batch {
   int graph_iters = 32;           // MM iterations per graph replay (even)
   cc_solve_opts opts{};
   hipStream_t stream = nullptr;   // private: graphs are captured on it
-  std::vector<hipStream_t> side;  // point and edge classes beyond the first, as graph branches
-  std::vector<hipEvent_t> ev;      // fork and join events of those branches
+  std::vector<hipStream_t> side;  // chains of the graph beyond the first
+  std::vector<hipEvent_t> ev;      // their fork and join events
   std::vector<int> order;         // instances by decreasing work
   BatchInst *bi = nullptr;
   std::vector<int> n_gamma;
@@ -325,7 +325,10 @@ struct Server {
   int64_t budget = 0, used = 0;
   int max_active = 64;
   int round_iters = 32;            // MM iterations per round (even)
-  int vec = 4, ipw = 4;
+  // tile shape of every request's point sweep: of 1, 2, 4, 8 items per wave 2
+  // is the fastest from 6 requests (26.0 ms; 26.9, 28.4, 30.2) to 96 (285;
+  // 303, 290, 303); features per lane by row length, in one kernel, no faster
+  int vec = 4, ipw = 2;
   hipStream_t stream = nullptr;    // not owned
   LaunchSet ls;
   bool dirty = false;

@@ -50,6 +50,7 @@
 #include <cstring>
 #include <new>
 #include <numeric>
+#include <tuple>
 #include <type_traits>
 
 #include "ccmi_internal.h"
@@ -1041,7 +1042,7 @@ __global__ __launch_bounds__(kEdgeBlock) void k_edge_items_batch(const EdgeArgs 
 // lane packed with the local block (kNvShift).  A round's launches follow
 // each other on one stream, where a launch per width left most of the chip
 // idle in each (12 requests of four widths: 18.7 + 13.4 + 11.8 + 11.7 us, here
-// 24).  A batch's graph runs the widths as parallel branches instead, in
+// 24).  A batch's graph runs the widths as parallel chains instead, in
 // kernels that fit more waves per SIMD (48 instances: 29 us, here 33).
 constexpr int kNvShift = 16;
 
@@ -2654,6 +2655,14 @@ __global__ void k_batch_done_ticks(int n_inst, const BatchInst *bi, unsigned lon
   if (b < n_inst) out[b] = *bi[b].t_done;
 }
 
+// f(std::integral_constant) of a precision
+template <typename F>
+static void by_precision(int prec, F f) {
+  if (prec == kF32) f(std::integral_constant<int, kF32>());
+  else if (prec == kF64) f(std::integral_constant<int, kF64>());
+  else f(std::integral_constant<int, kMixed>());
+}
+
 template <int PREC>
 static void launch_point_class(const PointClass &c, int par, hipStream_t st) {
   const dim3 g(c.nblk), t(kPointBlock);
@@ -2685,45 +2694,53 @@ static void launch_edge_class(const EdgeClass &c, int par, hipStream_t s) {
   }
 }
 
-// Launches of one class list; with side streams and events (graph capture)
-// the classes after the first run on their own streams as parallel branches
-// forked from and joined back into st (they cover disjoint instances).
-template <typename Cls, typename Fn>
-static void launch_branches(const std::vector<Cls> &cls, hipStream_t st, const hipStream_t *side,
-                            const hipEvent_t *ev, Fn launch) {
-  const int nc = (int)cls.size();
-  if (side && nc > 1) (void)hipEventRecord(ev[0], st);
-  for (int k = 0; k < nc; ++k) {
-    hipStream_t s = st;
-    if (side && k > 0) {
-      s = side[k - 1];
-      (void)hipStreamWaitEvent(s, ev[0], 0);
-    }
-    launch(cls[k], s);
-    if (side && k > 0) (void)hipEventRecord(ev[k], s);
+// One MM iteration of every problem of a set (scalar-slot parity par): every
+// point class, then every edge class.
+static void launch_set_iteration(const LaunchSet &L, int prec, int par, hipStream_t st) {
+  by_precision(prec, [&](auto PR) {
+    for (const PointClass &c : L.pcls) launch_point_class<decltype(PR)::value>(c, par, st);
+    for (const EdgeClass &c : L.ecls) launch_edge_class<decltype(PR)::value>(c, par, st);
+  });
+}
+
+// The iterations of a batch's graph.  Point class k and edge class k cover
+// the same instances, which no other class touches, so classes run through
+// all the iterations in chains of their own, forked from st once and joined
+// once (the chains after the first on side streams).  Joining the classes
+// after every sweep left two gaps of about 10 us in an iteration of 100 (48
+// instances of 50..800 x 20..200, three classes: 49.0 ms per batch, as chains
+// 38.9).  At most kChains: as many as the process has hardware queues.
+// Further classes are launched within the chain that has the fewest blocks
+// (rows of 20..1000, five classes: joined every sweep 139.5 ms, 5 chains
+// 124.2, 4 chains 115.9, 3 chains 116.2).
+constexpr int kChains = 4;
+
+static void launch_chains(const LaunchSet &L, int prec, int iters, hipStream_t st,
+                          const hipStream_t *side, const hipEvent_t *ev) {
+  const int n_cls = (int)L.pcls.size(), nc = std::min(n_cls, kChains);
+  std::vector<std::vector<int>> chain(nc);
+  std::vector<int64_t> load(nc, 0);
+  std::vector<int> by(n_cls);
+  std::iota(by.begin(), by.end(), 0);
+  std::stable_sort(by.begin(), by.end(), [&](int a, int b) { return L.pcls[a].nblk > L.pcls[b].nblk; });
+  for (int k : by) {
+    const int q = (int)(std::min_element(load.begin(), load.end()) - load.begin());
+    chain[q].push_back(k);
+    load[q] += L.pcls[k].nblk;
   }
-  if (side)
-    for (int k = 1; k < nc; ++k) (void)hipStreamWaitEvent(st, ev[k], 0);
-}
-
-// One iteration of a launch set: every point class, then every edge class.
-template <int PREC>
-static void launch_set_p(const LaunchSet &L, int par, hipStream_t st, const hipStream_t *side,
-                         const hipEvent_t *ev) {
-  launch_branches(L.pcls, st, side, ev, [&](const PointClass &c, hipStream_t s) {
-    if (c.nblk > 0) launch_point_class<PREC>(c, par, s);
-  });
-  launch_branches(L.ecls, st, side, ev, [&](const EdgeClass &c, hipStream_t s) {
-    launch_edge_class<PREC>(c, par, s);
-  });
-}
-
-// One MM iteration of every problem of the set (scalar-slot parity par).
-static void launch_set_iteration(const LaunchSet &L, int prec, int par, hipStream_t st,
-                                 const hipStream_t *side = nullptr, const hipEvent_t *ev = nullptr) {
-  if (prec == kF32) launch_set_p<kF32>(L, par, st, side, ev);
-  else if (prec == kF64) launch_set_p<kF64>(L, par, st, side, ev);
-  else launch_set_p<kMixed>(L, par, st, side, ev);
+  if (nc > 1) (void)hipEventRecord(ev[0], st);
+  for (int q = 0; q < nc; ++q) {
+    const hipStream_t s = q > 0 ? side[q - 1] : st;
+    if (q > 0) (void)hipStreamWaitEvent(s, ev[0], 0);
+    by_precision(prec, [&](auto PR) {
+      for (int it = 0; it < iters; ++it) {
+        for (int k : chain[q]) launch_point_class<decltype(PR)::value>(L.pcls[k], it & 1, s);
+        for (int k : chain[q]) launch_edge_class<decltype(PR)::value>(L.ecls[k], it & 1, s);
+      }
+    });
+    if (q > 0) (void)hipEventRecord(ev[q], s);
+  }
+  for (int k = 1; k < nc; ++k) (void)hipStreamWaitEvent(st, ev[k], 0);
 }
 
 template <typename T>
@@ -2794,39 +2811,39 @@ static cc_status build_launch_set(LaunchSet &L, const std::vector<Problem *> &pr
     }
     P->slot = 0;
   }
-  // point classes in order of first appearance along the instance order
-  std::vector<std::pair<int, int>> keys;
-  for (int b : order) {
-    const std::pair<int, int> k{vec_of[b], ipw_of[b]};
-    if (std::find(keys.begin(), keys.end(), k) == keys.end()) keys.push_back(k);
-  }
-  for (const auto &k : keys) {
+  // classes (features per lane and items per wave of the point sweep,
+  // features per lane of the edge sweep) in order of first appearance along
+  // the instance order; with one_edge the edge sweeps of every class share a
+  // launch (nv 0)
+  using Key = std::tuple<int, int, int>;
+  auto key_of = [&](int b) { return Key(vec_of[b], ipw_of[b], one_edge ? 0 : probs[b]->item_nv); };
+  std::vector<Key> keys;
+  for (int b : order)
+    if (std::find(keys.begin(), keys.end(), key_of(b)) == keys.end()) keys.push_back(key_of(b));
+  std::vector<int2> et;
+  for (const Key &k : keys) {
     std::vector<int2> pt;
-    for (int b : order)
-      if (vec_of[b] == k.first && ipw_of[b] == k.second)
-        for (int q = 0; q < pblocks[b]; ++q) pt.push_back(make_int2(b, q));
+    if (!one_edge) et.clear();
+    for (int b : order) {
+      if (key_of(b) != k) continue;
+      for (int q = 0; q < pblocks[b]; ++q) pt.push_back(make_int2(b, q));
+      for (int q = 0; q < eblocks[b]; ++q)
+        et.push_back(make_int2(b, one_edge ? probs[b]->item_nv << kNvShift | q : q));
+    }
     PointClass c;
-    c.vec = k.first;
-    c.ipw = k.second;
+    c.vec = std::get<0>(k);
+    c.ipw = std::get<1>(k);
     c.nblk = (int)pt.size();
     for (int par = 0; par < 2; ++par) CC_TRY(upload(&c.pargs[par], pa[par], st));
     CC_TRY(upload(&c.ptab, pt, st));
     L.pcls.push_back(c);
-  }
-  for (int nv : {0, 1, 2, 4, 8, 16}) {  // 0: every width
-    if ((nv == 0) != one_edge) continue;
-    std::vector<int2> et;
-    for (int b : order)
-      if (one_edge || probs[b]->item_nv == nv)
-        for (int q = 0; q < eblocks[b]; ++q)
-          et.push_back(make_int2(b, one_edge ? probs[b]->item_nv << kNvShift | q : q));
-    if (et.empty()) continue;
-    EdgeClass c;
-    c.nv = nv;
-    c.nblk = (int)et.size();
-    for (int par = 0; par < 2; ++par) CC_TRY(upload(&c.eargs[par], ea[par], st));
-    CC_TRY(upload(&c.etab, et, st));
-    L.ecls.push_back(c);
+    if (one_edge && k != keys.back()) continue;
+    EdgeClass e;
+    e.nv = std::get<2>(k);
+    e.nblk = (int)et.size();
+    for (int par = 0; par < 2; ++par) CC_TRY(upload(&e.eargs[par], ea[par], st));
+    CC_TRY(upload(&e.etab, et, st));
+    L.ecls.push_back(e);
   }
   CC_HIP(hipStreamSynchronize(st));
   return CC_OK;
@@ -2843,7 +2860,7 @@ static cc_status batch_configure(Batch *B, const std::vector<int> *order = nullp
   if (B->graph) (void)hipGraphDestroy(B->graph);
   B->gexec = nullptr;
   B->graph = nullptr;
-  const size_t nc = std::max(B->ls.ecls.size(), B->ls.pcls.size());
+  const size_t nc = std::min<size_t>(B->ls.pcls.size(), kChains);
   while (B->side.size() + 1 < nc) {
     hipStream_t s;
     CC_HIP(hipStreamCreateWithFlags(&s, hipStreamNonBlocking));
@@ -2855,8 +2872,7 @@ static cc_status batch_configure(Batch *B, const std::vector<int> *order = nullp
     B->ev.push_back(e);
   }
   CC_HIP(hipStreamBeginCapture(B->stream, hipStreamCaptureModeThreadLocal));
-  for (int it = 0; it < B->graph_iters; ++it)
-    launch_set_iteration(B->ls, B->precision, it & 1, B->stream, B->side.data(), B->ev.data());
+  launch_chains(B->ls, B->precision, B->graph_iters, B->stream, B->side.data(), B->ev.data());
   CC_HIP(hipStreamEndCapture(B->stream, &B->graph));
   CC_HIP(hipGraphInstantiate(&B->gexec, B->graph, nullptr, nullptr, 0));
   return CC_OK;
