@@ -115,7 +115,8 @@ TRAFFIC_PROFILES = {
     ("expression", "mixed"): os.path.join(ROOT, "profiles", "traffic_k_point_expression_n2000_p500_mixed.md"),
     ("genotype", "mixed"): os.path.join(ROOT, "profiles", "traffic_k_point_genotype_n1000_p20000_mixed.md"),
 }
-KERNEL_SOURCES = ("paper_1409_2065_amd/csrc/solver.hip", "paper_1409_2065_amd/csrc/ccmi_internal.h")
+KERNEL_SOURCES = tuple("paper_1409_2065_amd/csrc/" + f for f in
+                       ("solver.hip", "slab.hip", "sweep.h", "wave_ops.h", "ccmi_internal.h"))
 
 
 def kernel_source_hash():

@@ -243,7 +243,9 @@ cc_status cc_get_trace(cc_problem_t prob, double *F, int64_t cap,
  * statistics.  cc_kernel_stats (host outputs, 2 entries each: the point
  * sweep, which begins by finishing the previous iteration, then the edge
  * stage) returns the mean duration in milliseconds and the number of
- * sampled launches. */
+ * sampled launches.  A problem small enough to be solved by one resident
+ * workgroup has no launch per stage: its samples are taken by the device's
+ * clock inside the kernel. */
 cc_status cc_profile(cc_problem_t prob, int32_t sample_every);
 cc_status cc_kernel_stats(cc_problem_t prob, double *avg_ms, int64_t *launches);
 

@@ -20,12 +20,17 @@
 //             (group soft-threshold) are recomputed on the fly from the edge
 //             norms and d of iteration m-1.  Per-block FP64 partial sums feed
 //             d, the objective and the stopping test.
+//             (k_point_slab in slab.hip: the same sweep over LDS slabs, for
+//             wide rows of some hundreds of points)
 //   k_edge_items (rows up to 1024 wide: work items of edges sharing a lower
-//             end) or k_edge_slab_items / k_edge_slab / k_edge_tiles and
-//             k_edge_reduce (wider rows): per edge ||b_e|| of the new A, the
+//             end), k_edge_rows (wider rows, few edges) or k_edge_slab_items /
+//             k_edge_slab / k_edge_tiles and k_edge_reduce: per edge ||b_e|| of the new A, the
 //             terms of ||V - D A||^2 and of the penalty, and the q factors of
 //             the next sweep; each block also gathers a fixed subset of the
 //             point sweep's block partials into its partial row.
+//
+// A problem that fits one workgroup runs all its iterations in one launch
+// (resident.hip).
 //
 // Storage: the mixed precision keeps A as its FP32 gather copy plus an FP32
 // low half; single solves with one projection sweep do not store U during
