@@ -290,7 +290,8 @@ cc_status profile(Problem *P, int32_t sample_every);
 cc_status harvest_profile(Problem *P);
 cc_status components(int64_t n, int64_t E, const int32_t *ei,
                      const int32_t *ej, const uint8_t *keep, const double *s,
-                     int32_t *labels, int32_t *ncl_dev, hipStream_t stream, int count = 1);
+                     int32_t *labels, int32_t *ncl_dev, hipStream_t stream, int count = 1,
+                     const DevScalars *gate = nullptr);
 
 // Served solves: requests queue on the host, are admitted while the HBM
 // budget allows, and share launches with the other admitted requests.

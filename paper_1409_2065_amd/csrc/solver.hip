@@ -1527,11 +1527,13 @@ __global__ void k_fused_flags(int E, const double *s, uint8_t *out) {
 // at the end; more points keep them in memory.  Both reach the same labels:
 // hooking and jumping only ever lower a label towards the smallest index of
 // its component, and the rounds end when neither can.
+// gate (may be null): nothing is written unless that solve has ended well.
 template <bool LDS>
 __global__ __launch_bounds__(1024) void k_components(int n, int E, const int32_t *ei,
                                                      const int32_t *ej, const uint8_t *keep,
                                                      const double *s, int32_t *lab_out,
-                                                     int32_t *ncl) {
+                                                     int32_t *ncl, const DevScalars *gate) {
+  if (gate && (!gate->done || gate->status != 0)) return;  // uniform
   extern __shared__ int32_t lab_s[];
   __shared__ int changed;
   __shared__ int cnt_s[1024 / kWave];
@@ -2475,7 +2477,9 @@ cc_status solve(Problem *P, double gamma, const cc_solve_opts &o, cc_solve_info 
   int32_t *lab = labels ? labels : P->lab;
   auto enqueue_labels = [&]() -> cc_status {
     if (!info) return CC_OK;
-    CC_TRY(components(P->n, P->E, P->ei, P->ej, nullptr, P->s, lab, P->ncl_dev, P->stream));
+    // enqueued before the host knows how the solve ended: a failed one leaves
+    // the caller's row alone
+    CC_TRY(components(P->n, P->E, P->ei, P->ej, nullptr, P->s, lab, P->ncl_dev, P->stream, 1, P->sc + P->slot));
     CC_HIP(hipMemcpyAsync(P->flag_host, P->ncl_dev, 4, hipMemcpyDeviceToHost, P->stream));
     return CC_OK;
   };
@@ -2539,13 +2543,13 @@ cc_status solve(Problem *P, double gamma, const cc_solve_opts &o, cc_solve_info 
 
 cc_status components(int64_t n, int64_t E, const int32_t *ei, const int32_t *ej,
                      const uint8_t *keep, const double *s, int32_t *labels,
-                     int32_t *ncl_dev, hipStream_t stream, int count) {
+                     int32_t *ncl_dev, hipStream_t stream, int count, const DevScalars *gate) {
   if (n <= kLabelLds)
     hipLaunchKernelGGL((k_components<true>), dim3(count), dim3(1024), n * 4, stream, (int)n, (int)E,
-                       ei, ej, keep, s, labels, ncl_dev);
+                       ei, ej, keep, s, labels, ncl_dev, gate);
   else
     hipLaunchKernelGGL((k_components<false>), dim3(count), dim3(1024), 0, stream, (int)n, (int)E,
-                       ei, ej, keep, s, labels, ncl_dev);
+                       ei, ej, keep, s, labels, ncl_dev, gate);
   CC_HIP(hipGetLastError());
   return CC_OK;
 }
