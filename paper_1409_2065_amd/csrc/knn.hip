@@ -468,6 +468,25 @@ __global__ __launch_bounds__(1024) void k_max_norm(int n, const float *nrm, floa
   if (threadIdx.x == 0) *nmax = s[0];
 }
 
+// Order of (distance, row) pairs; a distance that is not a number comes
+// after every number.
+__device__ __forceinline__ bool dist_less(double a, int i, double b, int j) {
+  const bool an = a == a, bn = b == b;
+  if (an != bn) return an;
+  return an ? (a < b || (a == b && i < j)) : i < j;
+}
+
+// How a block of 256 threads ranks K exact distances for the k smallest.
+// Counting takes a step per candidate and turn of 256 candidates; finding
+// them in turn measured 12 such steps each at K = 512 and 37 at 2999.  The
+// first pass counts (K is about 2 k); a wide one finds a few of thousands
+// (12000 rows, k = 10: 76 ms for K = 11999, by counting 3342; K = 512 1.0 and
+// 1.9 ms).
+__device__ __forceinline__ bool rank_by_counting(int K, int k) {
+  const int turns = (K + 255) / 256;
+  return 2 * (int64_t)turns * K <= (int64_t)k * (5 * turns + 14);
+}
+
 // Exact FP64 squared distances of the candidates, then the k best by (d2, j).
 // Certificate: every row left out has an FP32 distance of at least dnext[i],
 // so an exact one of at least dnext[i] - bound, with bound = bscale *
@@ -483,7 +502,8 @@ __global__ __launch_bounds__(256) void k_recheck(int n, int p, const double *Xd,
                                                  int *n_uncert) {
   extern __shared__ double sd[];  // K doubles + K ints
   int *sj = reinterpret_cast<int *>(sd + K);
-  __shared__ double kth;
+  __shared__ double kth, wd[2][4];
+  __shared__ int wj[2][4];
   const int i = blockIdx.x;
   if (todo && !todo[i]) return;
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
@@ -501,22 +521,53 @@ __global__ __launch_bounds__(256) void k_recheck(int n, int p, const double *Xd,
   }
   if (threadIdx.x == 0) kth = NAN;  // no candidate of that rank: not certified
   __syncthreads();
-  // a candidate's rank is the number of smaller (d2, j); a thread per
-  // candidate counts it (one thread selecting them in turn took 3/4 of this
-  // kernel's time at K = 32).  A distance that is not a number ranks last,
-  // by row.
-  for (int c = threadIdx.x; c < K; c += blockDim.x) {
-    const double d = sd[c];
-    const int j = sj[c];
-    const bool num = d == d;
-    int r = 0;
-    for (int o = 0; o < K; ++o) {
-      const double od = sd[o];
-      const bool less = num ? (od < d || (od == d && sj[o] < j)) : (od == od || sj[o] < j);
-      r += less ? 1 : 0;
+  // The k smallest (d2, j), a distance that is not a number last, by row.
+  if (rank_by_counting(K, k)) {
+    // a candidate's rank is the number of smaller ones; a thread per
+    // candidate counts it (one thread selecting them in turn took 3/4 of this
+    // kernel's time at K = 32)
+    for (int c = threadIdx.x; c < K; c += blockDim.x) {
+      const double d = sd[c];
+      const int j = sj[c];
+      const bool num = d == d;
+      int r = 0;
+      for (int o = 0; o < K; ++o) {
+        const double od = sd[o];
+        const bool less = num ? (od < d || (od == d && sj[o] < j)) : (od == od || sj[o] < j);
+        r += less ? 1 : 0;
+      }
+      if (r < k) knn[(size_t)i * k + r] = j;
+      if (r == k - 1) kth = d;
     }
-    if (r < k) knn[(size_t)i * k + r] = j;
-    if (r == k - 1) kth = d;
+  } else {
+    // the block finds them in turn, each the smallest above the last
+    double last = 0.0;
+    int lj = -1;
+    for (int r = 0; r < k; ++r) {
+      double b = NAN;
+      int bj = INT32_MAX;
+      for (int c = threadIdx.x; c < K; c += blockDim.x) {
+        const double d = sd[c];
+        const int j = sj[c];
+        if (dist_less(last, lj, d, j) && dist_less(d, j, b, bj)) { b = d; bj = j; }
+      }
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) {
+        const double ob = __shfl_xor(b, off, kWave);
+        const int oj = __shfl_xor(bj, off, kWave);
+        if (dist_less(ob, oj, b, bj)) { b = ob; bj = oj; }
+      }
+      // two sets of slots in turn: one barrier per candidate
+      if (lane == 0) { wd[r & 1][wave] = b; wj[r & 1][wave] = bj; }
+      __syncthreads();
+      last = wd[r & 1][0];
+      lj = wj[r & 1][0];
+#pragma unroll
+      for (int w = 1; w < 4; ++w)
+        if (dist_less(wd[r & 1][w], wj[r & 1][w], last, lj)) { last = wd[r & 1][w]; lj = wj[r & 1][w]; }
+      if (threadIdx.x == 0) knn[(size_t)i * k + r] = lj;
+    }
+    if (threadIdx.x == 0) kth = last;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
