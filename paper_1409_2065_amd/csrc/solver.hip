@@ -1946,7 +1946,11 @@ cc_status harvest_profile(Problem *P) {
 }
 
 // Arrays cut from one device allocation, each 256-byte aligned; those given
-// as host vectors (from) are copied there together, from stage().
+// as host vectors (from) are copied there: the small ones together, from a
+// copy of them, the large ones each from where it is, so that lists of many
+// edges are not held and written twice on the host.
+constexpr size_t kStageBytes = (size_t)1 << 20;
+
 struct Carve {
   struct Part { void **slot; size_t at; const void *src; size_t len; };
   std::vector<Part> parts;
@@ -1964,6 +1968,14 @@ struct Carve {
     for (const Part &q : parts)
       if (q.src && q.len) std::memcpy(h.data() + q.at, q.src, q.len);
     return h;
+  }
+  hipError_t copy(hipStream_t st) const {  // each part by itself
+    for (const Part &q : parts)
+      if (q.src && q.len) {
+        const hipError_t e = hipMemcpyAsync(*q.slot, q.src, q.len, hipMemcpyHostToDevice, st);
+        if (e != hipSuccess) return e;
+      }
+    return hipSuccess;
   }
 };
 
@@ -2211,18 +2223,21 @@ cc_status problem_create(int64_t n, int64_t p, int32_t x_dtype, const void *X,
     const int64_t row = (e2 % 2 == 0) ? hi[e2 / 2] : hj[e2 / 2];
     hposE[e2] = (int32_t)ell_slot(row, k - rp[row]);
   }
-  // ---- device memory: one allocation, what is uploaded at its front ----
+  // ---- device memory: one allocation, what is uploaded together at its front ----
   // (an allocation costs the host about 10 us, a release 20, a copy 14)
   Carve up, mem;
-  up.from(&P->colE, hcolE); up.from(&P->eidE, heidE); up.from(&P->degE, hdegE);
-  up.from(&P->rowptr, rp); up.from(&P->uptr, hup);
-  up.from(&P->col, hcol); up.from(&P->eid, heid); up.from(&P->epos, hposE);
-  up.from(&P->ei, hi); up.from(&P->ej, hj); up.from(&P->w, hw);
-  up.from(&P->itemI, iI); up.from(&P->itemJ, iJ); up.from(&P->itemE, iE);
-  if (slab) up.from(&P->slab_order, P->slab.order);
+  auto put = [&](auto **slot, const auto &v) {
+    (v.size() * sizeof(v[0]) < kStageBytes ? up : mem).from(slot, v);
+  };
+  put(&P->colE, hcolE); put(&P->eidE, heidE); put(&P->degE, hdegE);
+  put(&P->rowptr, rp); put(&P->uptr, hup);
+  put(&P->col, hcol); put(&P->eid, heid); put(&P->epos, hposE);
+  put(&P->ei, hi); put(&P->ej, hj); put(&P->w, hw);
+  put(&P->itemI, iI); put(&P->itemJ, iJ); put(&P->itemE, iE);
+  if (slab) put(&P->slab_order, P->slab.order);
   if (resident) {
-    up.from(&P->res_order, P->res.order);
-    up.from(&P->res_estart, P->res.estart);
+    put(&P->res_order, P->res.order);
+    put(&P->res_estart, P->res.estart);
   }
   double *mean = nullptr, *dev2 = nullptr;  // dev2: p values, then the non-finite flag
   mem.add(&P->X, nl * tx_size(precision));
@@ -2251,7 +2266,8 @@ cc_status problem_create(int64_t n, int64_t p, int32_t x_dtype, const void *X,
   mem.place((char *)P->mem + up.bytes);
   if (precision != kMixed) { P->G[0] = P->A[0]; P->G[1] = P->A[1]; }
   const std::vector<char> stage = up.stage();
-  CC_HIP(hipMemcpyAsync(P->mem, stage.data(), stage.size(), hipMemcpyHostToDevice, stream));
+  if (!stage.empty()) CC_HIP(hipMemcpyAsync(P->mem, stage.data(), stage.size(), hipMemcpyHostToDevice, stream));
+  CC_HIP(mem.copy(stream));
   CC_HIP(hipMemsetAsync(P->res_prof, 0, 3 * 8, stream));
   constexpr size_t kScBytes = (sizeof(DevScalars) + 63) / 64 * 64;
   CC_HIP(hipHostMalloc((void **)&P->sc_host, kScBytes + 64, hipHostMallocDefault));
