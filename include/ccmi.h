@@ -292,7 +292,7 @@ cc_status cc_get_state(cc_problem_t prob, double *U, double *A, int64_t ld,
  * then over all rows (n <= 12289).  CC_ERR_NUMERIC when a row still cannot
  * be certified (only above that n, for rows with more than 12288 others
  * within FP32 rounding of their k-th neighbour).
- *   k           1 <= k < n.
+ *   k           1 <= k < n, k <= 12288.
  *   phi         >= 0 literal; < 0 means |phi| / median(d^2 over the edge
  *               set), the lower median.
  *   normalize   1: scale the weights to sum to 1 over the edge set (the

@@ -929,7 +929,7 @@ template <typename TI> struct KnnLists {
     ar = &a;
     n_pad = cdiv64(n, kGT) * kGT;
     ldk = cdiv64(p, kKC) * kKC;
-    K = (int)std::min<int64_t>(n - 1, (int64_t)k + std::max(16, k));
+    K = (int)std::min<int64_t>({n - 1, (int64_t)k + std::max(16, k), kRecheckMaxK});
     rows = std::min<int64_t>(n_pad, std::max<int64_t>(kPanelBytes / (4 * n) / kGT * kGT, kGT));
     // split the features until the launch has about 4 blocks per CU (at
     // most 8 splits)
@@ -1275,6 +1275,7 @@ cc_status build_knn_weights(int64_t n, int64_t p, int32_t x_dtype, const void *X
   if (n > kKnnMaxN) { set_error("cc_build_knn_weights supports n <= 16384"); return CC_ERR_INVALID_ARG; }
   if ((int64_t)n * p > ((int64_t)1 << 31) - 1) { set_error("n * p too large"); return CC_ERR_INVALID_ARG; }
   if (k < 1 || k >= n) { set_error("need 1 <= k < n"); return CC_ERR_INVALID_ARG; }
+  if (k > kRecheckMaxK) { set_error("cc_build_knn_weights supports k <= 12288"); return CC_ERR_INVALID_ARG; }
   if (!X || !ei || !ej || !w || !n_edges) { set_error("NULL argument"); return CC_ERR_INVALID_ARG; }
   if (x_dtype != CC_DTYPE_F32 && x_dtype != CC_DTYPE_F64) { set_error("bad x_dtype"); return CC_ERR_INVALID_ARG; }
   if (ldx < p || (mask && ldm < p)) { set_error("leading dimension < p"); return CC_ERR_INVALID_ARG; }

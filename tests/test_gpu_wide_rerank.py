@@ -32,3 +32,22 @@ def test_wide_passes_rank_exactly(cc, n, groups, spread, k):
     assert np.array_equal(e.cpu().numpy(), e0)
     assert np.allclose(w.cpu().numpy(), w0, rtol=1e-12, atol=0)
     assert phi == phi0
+
+
+def test_more_neighbours_than_half_the_candidates(cc):
+    """7000 neighbours of 14010 rows: twice k is more than a pass takes, so it
+    ranks 12288 candidates.  The neighbours of some rows against the oracle's
+    lists of those rows and of the rows they meet."""
+    n, k = 14010, 7000
+    rng = np.random.default_rng(5)
+    X = rng.standard_normal((n, 2))
+    e = cc.build_knn_weights(torch.tensor(X, device="cuda"), None, k=k, phi=0.5)[0]
+    for i in (0, 77, n - 1):
+        lists = weights.knn_rows(X, k, [i])
+        nb = torch.cat([e[e[:, 0] == i, 1], e[e[:, 1] == i, 0]]).cpu().numpy()
+        assert len(set(nb)) == len(nb) and set(lists[0]) <= set(nb)
+        extra = np.setdiff1d(nb, lists[0])
+        out = np.setdiff1d(np.arange(n), np.append(nb, i))
+        for js, there in ((extra, True), (out, False)):
+            for j in rng.permutation(js)[:5]:
+                assert (i in weights.knn_rows(X, k, [j])[0]) == there
