@@ -2506,9 +2506,12 @@ cc_status solve(Problem *P, double gamma, const cc_solve_opts &o, cc_solve_info 
     for (int64_t it = 0; it <= last; it += chunk) {
       const int iters = (int)std::min<int64_t>(chunk, last + 1 - it);
       CC_TRY(resident_run(P, iters));
-      P->prof_iter += iters;
       CC_TRY(enqueue_labels());
       CC_TRY(read_scalars(P));
+      // the sampling goes on from the sweeps that ran: all of a launch that
+      // did not end the solve, 0 .. iters of a solve in all
+      const int64_t ran = P->sc_host->done ? (int64_t)P->sc_host->iters + 1 - it : iters;
+      P->prof_iter += ran;
       if (P->sc_host->done) break;
     }
     if (P->prof_every > 0) CC_TRY(harvest_resident(P));
