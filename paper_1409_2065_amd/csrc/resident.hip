@@ -384,7 +384,8 @@ bool resident_plan(int64_t n, int64_t ld, int64_t E, const int32_t *deg, int pre
   const char *env = getenv("CCMI_RESIDENT");
   if (env && atoi(env) == 0) return false;
   // a launch-shape switch asks for the sweeps over many blocks
-  for (const char *v : {"CCMI_VEC", "CCMI_IPW", "CCMI_EDGE_IPW", "CCMI_POINT_WAVES", "CCMI_SLAB_F", "CCMI_EDGE_ITEMS"})
+  for (const char *v : {"CCMI_VEC", "CCMI_IPW", "CCMI_EDGE_IPW", "CCMI_POINT_WAVES", "CCMI_SLAB_F", "CCMI_EDGE_ITEMS",
+                        "CCMI_EDGE_SLAB", "CCMI_EDGE_SLAB_ITEMS", "CCMI_LAZY_U"})
     if (getenv(v) && !(env && atoi(env) == 1)) return false;
   constexpr int64_t kResWork = 17000;
   if (n >= 65536 || E >= 65535 || n * ld > 65536 || 2 * E * (ld / 4) > kResWork) return false;
