@@ -1,5 +1,6 @@
-"""Which small problems one workgroup solves, and what the launch-shape
-switches turn off.
+"""Small problems by launches over many blocks, which the defaults solve in
+one workgroup: the inputs and tolerances of the tests of those solves, with
+CCMI_RESIDENT=0, and what the launch-shape switches turn off.
 
 A solve of I iterations by launches enqueues I + 2 pairs of them, a resident
 one runs I + 1 sweeps: the sampled counts tell which ran."""
@@ -7,6 +8,8 @@ import pytest
 import torch
 
 from tests import test_gpu_lazy_u as lazy_tests
+from tests import test_gpu_solver as solver_tests
+from tests import test_gpu_wide as wide_tests
 from tests._gpu import plain_problem, reduced_expression, to_dev
 
 pytestmark = pytest.mark.gpu
@@ -20,6 +23,11 @@ def cc():
     import paper_1409_2065_amd as P
     P.load()
     return P
+
+
+@pytest.fixture
+def launches(monkeypatch):
+    monkeypatch.setenv("CCMI_RESIDENT", "0")
 
 
 def ran_resident(cc, X, M, E, w, precision="mixed"):
@@ -57,3 +65,53 @@ def test_lazy_u_without_a_mask(cc, monkeypatch):
         monkeypatch.setenv("CCMI_LAZY_U", lazy)
         assert not ran_resident(cc, X, M, E, w)
     lazy_tests.test_lazy_u_no_mask_plain(cc, monkeypatch)
+
+
+@pytest.mark.parametrize("n,p", [(1, 1), (1, 5), (2, 1), (3, 300), (9, 1)])
+def test_tiny_shapes(cc, launches, n, p):
+    solver_tests.test_tiny_shapes(cc, n, p)
+
+
+@pytest.mark.parametrize("iters", [1, 2, 3, 7, 60])
+def test_trajectory(cc, launches, iters):
+    solver_tests.test_fixed_iterations_f64_match_oracle_trajectory(cc, iters)
+
+
+def test_stopping_test(cc, launches):
+    solver_tests.test_plain_config_f64_gamma_1(cc)
+
+
+@pytest.mark.parametrize("gamma", [10.0, 1000.0])
+def test_converged_mixed(cc, launches, gamma):
+    solver_tests.test_plain_config_mixed_converged(cc, gamma)
+
+
+def test_f32(cc, launches):
+    solver_tests.test_f32_precision_plain(cc)
+
+
+def test_no_edges(cc, launches):
+    solver_tests.test_gamma_zero_and_isolated_points(cc)
+
+
+def test_all_observed_mask(cc, launches):
+    solver_tests.test_all_observed_mask_equals_no_mask(cc)
+
+
+def test_non_finite_state(cc, launches):
+    solver_tests.test_non_finite_state_reports_numeric_error(cc)
+
+
+def test_sampling(cc, launches):
+    """Events of every fourth launch pair of 66: 17 samples."""
+    solver_tests.test_kernel_stats_sample_every_kth_iteration(cc)
+    X, M, E, w = plain_problem()
+    Xt, m, e, wt = to_dev(X, M, E, w, torch.float32)
+    with cc.Problem(Xt, m, e, wt) as g:
+        g.profile(4)
+        g.solve(10.0, tol=0.0, max_iter=64)
+        assert g.kernel_stats()["edge_stage"]["launches"] == 17
+
+
+def test_one_wide_edge(cc, launches):
+    wide_tests.test_edge_rows(cc, 2, 1025, 1, "f64", 1e-11)
