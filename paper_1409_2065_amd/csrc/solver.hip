@@ -3495,18 +3495,25 @@ Request *server_find(Server *S, int64_t ticket) {
   return nullptr;
 }
 
+constexpr int64_t kLabelScratch = (int64_t)64 << 20;
+
 cc_status server_result(Server *S, Request *R, int32_t *labels, cc_solve_info *infos) {
   if (R->state == CC_REQ_FAILED) { set_error("admission failed: " + R->error); return (cc_status)R->status; }
   if (R->state != CC_REQ_DONE) { set_error("request not done"); return CC_ERR_STATE; }
   Problem *P = R->P;
   const int ng = (int)R->gammas.size();
-  // a block per gamma; the counts come back with one copy
+  // a block per gamma; the counts come back with one copy.  Labels that
+  // nobody asked for go to a scratch of at most kLabelScratch, which many
+  // gammas share in turns
   std::vector<int32_t> ncl(ng, 0);
   if (labels || infos) {
-    int32_t *tmp = nullptr;  // labels that nobody asked for
+    int32_t *tmp = nullptr;
     struct Tmp { int32_t *&p; ~Tmp() { if (p) (void)hipFree(p); } } guard{tmp};
-    if (!labels) CC_TRY(dmalloc((void **)&tmp, (size_t)ng * P->n * 4));
-    CC_TRY(components(P->n, P->E, P->ei, P->ej, R->fused, nullptr, labels ? labels : tmp, R->ncl, S->stream, ng));
+    const int64_t row = P->n * 4, per = labels ? ng : std::min<int64_t>(ng, std::max<int64_t>(kLabelScratch / row, 1));
+    if (!labels) CC_TRY(dmalloc((void **)&tmp, (size_t)(per * row)));
+    for (int64_t g = 0; g < ng; g += per)
+      CC_TRY(components(P->n, P->E, P->ei, P->ej, R->fused + g * P->E, nullptr, labels ? labels : tmp, R->ncl + g,
+                        S->stream, (int)std::min<int64_t>(per, ng - g)));
     CC_HIP(hipMemcpyAsync(ncl.data(), R->ncl, ng * 4, hipMemcpyDeviceToHost, S->stream));
     CC_HIP(hipStreamSynchronize(S->stream));
   }
