@@ -322,6 +322,13 @@ __global__ void k_q_from_s(int64_t slots, const int32_t *colE, const int32_t *ei
 static inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 constexpr int64_t kPointSlabBytes = 140 * 1024;  // LDS of a slab and its group's points
 
+// Few points leave most lanes of a block idle, and a small state is over
+// before the staging pays (point sweep by waves and by slabs, us): 100 x
+// 60000 53 and 65, 300 x 8000 31 and 22, 300 x 2000 with a mask 14 and 15,
+// 1000 x 1000 with a mask 23 and 26, 1000 x 2000 41 and 26, with a mask 43
+// and 33, 1000 x 20000 212 and 173.
+bool slab_by_size(int64_t n, int64_t ld) { return n >= 256 && n * ld >= 1500000; }
+
 // The split of a slab sweep; false when the slab does not fit or the
 // wave-per-item sweep is as fast (or asked for).
 bool slab_plan(int64_t n, int64_t ld, const int32_t *deg, int prec, SlabPlan *plan) {
@@ -333,12 +340,7 @@ bool slab_plan(int64_t n, int64_t ld, const int32_t *deg, int prec, SlabPlan *pl
   if (!plan->forced) {
     for (const char *v : {"CCMI_VEC", "CCMI_IPW", "CCMI_POINT_WAVES"})
       if (getenv(v)) return false;
-    // Few points leave most lanes of a block idle, and a small state is over
-    // before the staging pays (point sweep by waves and by slabs, us): 100 x
-    // 60000 53 and 65, 300 x 8000 31 and 22, 300 x 2000 with a mask 14 and 15,
-    // 1000 x 1000 with a mask 23 and 26, 1000 x 2000 41 and 26, with a mask 43
-    // and 33, 1000 x 20000 212 and 173.
-    if (n < 256 || n * ld < 1500000) return false;
+    if (!slab_by_size(n, ld)) return false;
   }
   const int64_t tiles = cdiv(ld, kSlabF), per = kSlabNT / 4;
   // A block per CU (the slab takes most of its LDS).  With more tiles than

@@ -2060,12 +2060,20 @@ static void choose_tiles(Problem *P) {
     const char *ee = getenv("CCMI_EDGE_SLAB");
     const bool allow = !ee || atoi(ee) != 0;
     // whole rows, one launch, while the rows read (2 per edge) cost the L2s
-    // less than staging and reducing slabs does: at 289 MB (1000 x 3000, 12 000
-    // edges) 22.5 against 39.4 us, at 395 MB (1000 x 6000) 32.3 and 37.7; FP64
-    // at 236 MB (300 x 8000) 19.7 and 19.0.  A block per edge where edges are
-    // few against the row's length (170 edges of 4682 features: 5.2 us, by
+    // less than staging and reducing slabs does (us per iteration by rows and
+    // by slabs): at 116 MiB (1000 x 3000) 41 and 47, at 102 (1000 x 2000) 40
+    // and 51, the stage alone at 275 MiB (1000 x 3000) 22.5 and 39.4, at 377
+    // (1000 x 6000) 32.3 and 37.7; FP64 at 205 MiB (1000 x 2000) 62 and 72, at 231 (1000 x
+    // 3000) 73 and 76.  In FP64 beside the slab point sweep the edge slabs
+    // find their tiles in the L2 that just wrote them, and whole rows push
+    // those tiles out of it: 300 x 8000 at 90 and 172 MiB 36.5 and 31.8, 39.5
+    // and 34.5, 256 x 16000 52.5 and 45.6, 500 x 8000 45.8 and 41.2, 500 x 4000
+    // and 256 x 6000 within 1 us; slabs of 16 features, for up to 512 points
+    // (540 x 3000 by slabs of 8: 47.9 and 48.4).  A block per edge where edges
+    // are few against the row's length (170 edges of 4682 features: 5.2 us, by
     // waves 8.5), else a wave (650 of 1100: 5.5 us, by blocks 8.6)
-    if (!ee && !getenv("CCMI_EDGE_SLAB_ITEMS") &&
+    const bool tiles_in_l2 = P->precision == kF64 && P->edge_f == 16 && slab_by_size(P->n, P->ld);
+    if (!ee && !getenv("CCMI_EDGE_SLAB_ITEMS") && !tiles_in_l2 &&
         2 * P->E * P->ld * tg <= (tg == 4 ? kEdgeRowBytes4 : kEdgeRowBytes8)) {
       P->erows = 16 * P->E <= P->ld ? kEdgeWaves : 1;
       P->entile = 1;
