@@ -377,9 +377,20 @@ static int edge_lanes_log2(int64_t E, int64_t ld, int64_t threads) {
 // Whether a problem is solved resident, and its block.  deg: degrees of the
 // points.  The limits are the LDS, 16-bit neighbours, edges and list starts,
 // and the work: launches over many CUs take about 12 us an iteration
-// whatever the size up to some 10^5 features, one CU takes 10.8 us at 16 000
-// neighbour pieces a sweep (370 x 10, 2647 edges), 12 at 15 700 (50 x 200) and
-// 15 at 31 000 (100 x 100).
+// whatever the size up to some 10^5 features, one CU's time follows the
+// neighbour pieces of a sweep.  Near the limit of 17 000, resident and by
+// launches (us, FP32 / mixed / FP64): 340 x 10 (14 500 to 14 900 pieces) 9.5 /
+// 9.8 / 10.1 and 13.1, with a mask 9.6 / 10.0 / 10.4 and 12.9; 370 x 10 (16 000) 10.6 /
+// 10.9 and 13.2, with a mask 11.1 / 11.4 and 13.6 (FP64 does not fit); 100 x 60 (15 800)
+// 9.5 / 9.8 / 9.8 and 11.0 to 12.2; 40 x 250 (15 000) 10.8 / 11.4 and 11.9; beyond it 100 x 100
+// (31 000) 15 and 12.
+// Rows of more than 1024 features: an edge's 8 lanes walk its rows in series,
+// where the launches give it a wave or a block, and points take more turns of
+// the block's threads.  3 x 1100 7.1 / 7.2 / 6.5 and 11.4 to 12, 8 x 1100 10.4 / 10.8
+// / 9.6 and 11.8 to 12.2, 3 x 2000 9.9 / 10.1 / 9.2 and 11.6 to 12; 10 x 1100 11.4 / 11.9 and
+// 11.9 / 12.0; 5 x 2000 12.3 / 12.6 and 11.7 / 11.9, 10 x 1200 12.1 / 12.8 and 12.0, 9 x
+// 1400 12.1 / 12.7 and 11.8 / 12.0, 6 x 2000 14.6 / 15.1 and 11.9, 3 x 3000 13.7 / 14.1 / 12.6
+// and 11.5 to 12, 2 x 4000 15.6 / 15.7 / 14.1 and 11.6.
 bool resident_plan(int64_t n, int64_t ld, int64_t E, const int32_t *deg, int prec, ResidentPlan *plan) {
   const char *env = getenv("CCMI_RESIDENT");
   if (env && atoi(env) == 0) return false;
@@ -389,6 +400,7 @@ bool resident_plan(int64_t n, int64_t ld, int64_t E, const int32_t *deg, int pre
     if (getenv(v) && !(env && atoi(env) == 1)) return false;
   constexpr int64_t kResWork = 17000;
   if (n >= 65536 || E >= 65535 || n * ld > 65536 || 2 * E * (ld / 4) > kResWork) return false;
+  if (ld > 1024 && (ld > 2048 || n * (ld / 4) > 2304)) return false;
   int64_t NE = 0;
   std::vector<int32_t> estart(n), order(n);
   for (int64_t i = 0; i < n; ++i) {

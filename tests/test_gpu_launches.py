@@ -115,3 +115,13 @@ def test_sampling(cc, launches):
 
 def test_one_wide_edge(cc, launches):
     wide_tests.test_edge_rows(cc, 2, 1025, 1, "f64", 1e-11)
+
+
+@pytest.mark.parametrize("n,p,resident", [(8, 1024, True), (8, 1025, True), (8, 1152, True), (8, 1153, False),
+                                          (2, 2048, True), (2, 2049, False), (3, 3000, False), (10, 1200, False)])
+def test_which_wide_rows_run_resident(cc, n, p, resident):
+    """Both sides of the lines for rows of more than 1024 features; what runs
+    follows the oracle."""
+    X, M, E, w = wide_tests.problem(n, p, min(2, n - 1), False)
+    assert ran_resident(cc, X, M, E, w) == resident
+    wide_tests.follow(cc, X, M, E, w, "mixed", 3.0, 15, 2e-6)
