@@ -268,6 +268,7 @@ cc_status resident_run(Problem *P, int iters);
 struct PointArgs;
 bool slab_by_size(int64_t n, int64_t ld);  // whether the slabs pay, where they fit
 bool slab_plan(int64_t n, int64_t ld, const int32_t *deg, int prec, SlabPlan *plan);
+hipError_t slab_lds_limit(int prec, bool masked);
 void launch_point_slab(Problem *P, const PointArgs &a);
 void launch_slab_start(Problem *P);
 

@@ -377,10 +377,16 @@ bool slab_plan(int64_t n, int64_t ld, const int32_t *deg, int prec, SlabPlan *pl
   return true;
 }
 
+// The LDS limit of a problem's slab kernel: once, when it is created.
+hipError_t slab_lds_limit(int prec, bool masked) {
+  const void *k = masked ? (const void *)k_point_slab<kMixed, true> : (const void *)k_point_slab<kMixed, false>;
+  if (prec == kF32) k = masked ? (const void *)k_point_slab<kF32, true> : (const void *)k_point_slab<kF32, false>;
+  if (prec == kF64) k = masked ? (const void *)k_point_slab<kF64, true> : (const void *)k_point_slab<kF64, false>;
+  return hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kPointSlabBytes);
+}
+
 template <int PREC, bool MASK>
 static void launch_slab(Problem *P, const PointArgs &a) {
-  (void)hipFuncSetAttribute((const void *)k_point_slab<PREC, MASK>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)kPointSlabBytes);
   const SlabArgs sl{P->slab.tiles, P->slab.tpb, P->slab.groups, P->slab.pg,
                     reinterpret_cast<const int2 *>(P->slab_order)};
   klaunch(k_point_slab<PREC, MASK>, dim3(P->slab.blocks), dim3(kSlabNT), P->slab.lds, P->stream, P->pev[0], P->pev[1],

@@ -2202,6 +2202,7 @@ cc_status problem_create(int64_t n, int64_t p, int32_t x_dtype, const void *X,
   }
   P->nbe = edge_rows(P);
   const bool slab = slab_plan(n, P->ld, deg.data(), precision, &P->slab);
+  if (slab) CC_HIP(slab_lds_limit(precision, mask != nullptr));
   const bool resident =
       !P->slab.forced && resident_plan(n, P->ld, E, deg.data(), precision, &P->res);
   // ELL copy of the neighbour lists for the point sweep

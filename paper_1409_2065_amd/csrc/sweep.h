@@ -85,11 +85,6 @@ template <> struct VecIO<4> {
     *reinterpret_cast<double2 *>(p) = make_double2(v[0], v[1]);
     *reinterpret_cast<double2 *>(p + 2) = make_double2(v[2], v[3]);
   }
-  __device__ static void load_mask(const uint8_t *p, bool (&o)[4]) {
-    uint32_t v = *reinterpret_cast<const uint32_t *>(p);
-    o[0] = (v & 0xffu) != 0; o[1] = (v & 0xff00u) != 0;
-    o[2] = (v & 0xff0000u) != 0; o[3] = (v & 0xff000000u) != 0;
-  }
 };
 template <> struct VecIO<2> {
   __device__ static void load(const float *p, double (&o)[2]) {
@@ -106,17 +101,12 @@ template <> struct VecIO<2> {
   __device__ static void store(double *p, const double (&v)[2]) {
     *reinterpret_cast<double2 *>(p) = make_double2(v[0], v[1]);
   }
-  __device__ static void load_mask(const uint8_t *p, bool (&o)[2]) {
-    uint16_t v = *reinterpret_cast<const uint16_t *>(p);
-    o[0] = (v & 0xffu) != 0; o[1] = (v & 0xff00u) != 0;
-  }
 };
 template <> struct VecIO<1> {
   __device__ static void load(const float *p, double (&o)[1]) { o[0] = *p; }
   __device__ static void load(const double *p, double (&o)[1]) { o[0] = *p; }
   __device__ static void store(float *p, const double (&v)[1]) { *p = (float)v[0]; }
   __device__ static void store(double *p, const double (&v)[1]) { *p = v[0]; }
-  __device__ static void load_mask(const uint8_t *p, bool (&o)[1]) { o[0] = *p != 0; }
 };
 
 // Raw mask bytes of VEC consecutive entries (byte v in bits 8v..8v+7).
