@@ -52,12 +52,12 @@ __global__ __launch_bounds__(1024) void k_col_moments(int n, int p, const TI *X,
   constexpr int RG = 1024 / CPB, NW = 1024 / kWave;
   __shared__ double ssum[NW][CPB];
   __shared__ int scnt[NW][CPB];
-  __shared__ int sbad;
+  __shared__ int sbad, sflat;
   const int c = threadIdx.x % CPB, g = threadIdx.x / CPB, wave = threadIdx.x / kWave;
   const int f = blockIdx.x * CPB + c;
   const bool col = f < p;
   const int fc = col ? f : 0;
-  if (threadIdx.x == 0) sbad = 0;
+  if (threadIdx.x == 0) sbad = sflat = 0;
   // fn(x) for every row of this thread that counts; returns the bad ones
   auto rows = [&](auto fn) {
     int bad = 0;
@@ -80,18 +80,18 @@ __global__ __launch_bounds__(1024) void k_col_moments(int n, int p, const TI *X,
     }
     return bad;
   };
-  // column totals of a value per thread within a wave: lanes
-  // CPB apart
-  auto lanes = [&](auto v) {
+  // a column's values within a wave combined: lanes CPB apart
+  auto lanes = [&](auto v, auto op) {
 #pragma unroll
-    for (int off = kWave / 2; off >= CPB; off >>= 1) v += __shfl_xor(v, off, kWave);
+    for (int off = kWave / 2; off >= CPB; off >>= 1) v = op(v, __shfl_xor(v, off, kWave));
     return v;
   };
+  auto add = [](auto a, auto b) { return a + b; };
   double sum = 0.0;
   int cnt = 0;
   const int bad = rows([&](double x) { sum += x; ++cnt; });
-  sum = lanes(sum);
-  cnt = lanes(cnt);
+  sum = lanes(sum, add);
+  cnt = lanes(cnt, add);
   if (threadIdx.x % kWave < CPB) { ssum[wave][c] = sum; scnt[wave][c] = cnt; }
   __syncthreads();
   if (bad && col) atomicAdd(&sbad, bad);
@@ -106,15 +106,39 @@ __global__ __launch_bounds__(1024) void k_col_moments(int n, int p, const TI *X,
   if (!sec) return;
   double ss = 0.0;
   rows([&](double x) { ss += (x - mu) * (x - mu); });
-  ss = lanes(ss);
+  ss = lanes(ss, add);
   if (threadIdx.x % kWave < CPB) ssum[wave][c] = ss;
   __syncthreads();
+  bool flat = false;
   if (threadIdx.x < CPB && col) {
     double t = 0.0;
 #pragma unroll
     for (int w = 0; w < NW; ++w) t += ssum[w][c];
     sec[f] = root ? (tc > 0 ? sqrt(t / tc) : 0.0) : t;
+    // deviations within the rounding of the sum the mean came from
+    const double r = 0x1p-52 * tc * mu;
+    flat = root && t > 0.0 && t <= tc * r * r;
+    if (flat) sflat = 1;
   }
+  if (!root) return;
+  __syncthreads();
+  if (!sflat) return;
+  // some column may hold one value, off whose mean it rounds: such a column
+  // has a deviation of 0 exactly
+  double lo = INFINITY, hi = -INFINITY;
+  rows([&](double x) { lo = fmin(lo, x); hi = fmax(hi, x); });
+  lo = lanes(lo, [](double a, double b) { return fmin(a, b); });
+  hi = lanes(hi, [](double a, double b) { return fmax(a, b); });
+  if (threadIdx.x % kWave < CPB) ssum[wave][c] = lo;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < NW; ++w) lo = fmin(lo, ssum[w][c]);
+  __syncthreads();
+  if (threadIdx.x % kWave < CPB) ssum[wave][c] = hi;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < NW; ++w) hi = fmax(hi, ssum[w][c]);
+  if (flat && lo == hi) sec[f] = 0.0;
 }
 
 template <typename TI>
