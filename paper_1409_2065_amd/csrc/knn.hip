@@ -506,7 +506,7 @@ __device__ __forceinline__ bool dist_less(double a, int i, double b, int j) {
 // first pass counts (K is about 2 k); a wide one finds a few of thousands
 // (12000 rows, k = 10: 76 ms for K = 11999, by counting 3342; K = 512 1.0 and
 // 1.9 ms).
-__device__ __forceinline__ bool rank_by_counting(int K, int k) {
+static bool rank_by_counting(int K, int k) {
   const int turns = (K + 255) / 256;
   return 2 * (int64_t)turns * K <= (int64_t)k * (5 * turns + 14);
 }
@@ -519,6 +519,7 @@ __device__ __forceinline__ bool rank_by_counting(int K, int k) {
 // candidates are then the k nearest of all rows when the k-th exact distance
 // lies below that; otherwise uncert[i] = 1 and the row is counted in *n_uncert.
 // todo (may be NULL): only rows with todo[i] != 0.
+template <bool COUNT>
 __global__ __launch_bounds__(256) void k_recheck(int n, int p, const double *Xd, int K, int k,
                                                  const int32_t *cand, int32_t *knn, const int *todo,
                                                  const float *dnext, const float *nrm,
@@ -526,8 +527,7 @@ __global__ __launch_bounds__(256) void k_recheck(int n, int p, const double *Xd,
                                                  int *n_uncert) {
   extern __shared__ double sd[];  // K doubles + K ints
   int *sj = reinterpret_cast<int *>(sd + K);
-  __shared__ double kth, wd[2][4];
-  __shared__ int wj[2][4];
+  __shared__ double kth;
   const int i = blockIdx.x;
   if (todo && !todo[i]) return;
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
@@ -546,7 +546,7 @@ __global__ __launch_bounds__(256) void k_recheck(int n, int p, const double *Xd,
   if (threadIdx.x == 0) kth = NAN;  // no candidate of that rank: not certified
   __syncthreads();
   // The k smallest (d2, j), a distance that is not a number last, by row.
-  if (rank_by_counting(K, k)) {
+  if constexpr (COUNT) {
     // a candidate's rank is the number of smaller ones; a thread per
     // candidate counts it (one thread selecting them in turn took 3/4 of this
     // kernel's time at K = 32)
@@ -565,6 +565,8 @@ __global__ __launch_bounds__(256) void k_recheck(int n, int p, const double *Xd,
     }
   } else {
     // the block finds them in turn, each the smallest above the last
+    __shared__ double wd[2][4];
+    __shared__ int wj[2][4];
     double last = 0.0;
     int lj = -1;
     for (int r = 0; r < k; ++r) {
@@ -983,10 +985,6 @@ template <typename TI> struct KnnLists {
     hipLaunchKernelGGL(k_rownorm, dim3((int)n_pad), dim3(256), 0, st, (int)n_pad, (int)ldk, ar->at<float>(Xf),
                        ar->at<float>(nrm));
     hipLaunchKernelGGL(k_max_norm, dim3(1), dim3(1024), 0, st, (int)n, ar->at<float>(nrm), ar->at<float>(nmax));
-    // the dynamic LDS limit is set to the largest size the kernel takes
-    // (the same value on every call, so that concurrent builds agree)
-    CC_HIP(hipFuncSetAttribute((const void *)k_recheck, hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)(kRecheckMaxK * 12)));
     CC_HIP(hipGetLastError());
     return CC_OK;
   }
@@ -1018,8 +1016,15 @@ template <typename TI> struct KnnLists {
     // rounding bound of the FP32 distances (see k_recheck): (2 m + 24) u with
     // m the longest FP32 accumulation (ldk products and the split combine)
     const double bscale = (2.0 * (double)(ldk + nsplit) + 24.0) * std::ldexp(1.0, -24) * 1.001;
-    hipLaunchKernelGGL(k_recheck, dim3((int)n), dim3(256), (size_t)Kp * 12, st, (int)n, (int)p, ar->at<double>(Xd),
-                       Kp, k, cp, ar->at<int32_t>(knn), todo, ar->at<float>(dnext), ar->at<float>(nrm),
+    const auto recheck = rank_by_counting(Kp, k) ? k_recheck<true> : k_recheck<false>;
+    // beyond what any kernel may take, the dynamic LDS limit is set to the
+    // largest size (the same value on every call, so that concurrent builds
+    // agree)
+    if (Kp * 12 > 64 * 1024)
+      CC_HIP(hipFuncSetAttribute((const void *)recheck, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                 (int)(kRecheckMaxK * 12)));
+    hipLaunchKernelGGL(recheck, dim3((int)n), dim3(256), (size_t)Kp * 12, st, (int)n, (int)p, ar->at<double>(Xd), Kp,
+                       k, cp, ar->at<int32_t>(knn), todo, ar->at<float>(dnext), ar->at<float>(nrm),
                        ar->at<float>(nmax), bscale, ar->at<int>(uncert), n_uncert());
     CC_HIP(hipGetLastError());
     return CC_OK;
