@@ -17,8 +17,8 @@
 // orthogonal with norms sigma^2, it is as accurate as Gram-Schmidt.  Columns
 // that are nearly dependent (a pivot small against its column: a new start,
 // a spectrum that falls by orders of magnitude, fewer than s nonzero singular
-// values) are orthonormalised by Gram-Schmidt in two passes instead, as the
-// last step's always are.
+// values) are orthonormalised by Gram-Schmidt instead, as the last step's
+// always are.
 // Each column of V is signed so that its entry of largest magnitude (the
 // first such on ties) is positive.
 #include <hip/hip_runtime.h>
@@ -239,50 +239,66 @@ __device__ inline void sum_grams(int s, int blocks, const double *gram, double *
   __syncthreads();
 }
 
-// Gram-Schmidt in two passes over the columns of Q (p x s): each pass takes
-// the inner products with all earlier columns at once.  A column that
+// Gram-Schmidt over the columns of Q (p x s): a pass takes the inner products
+// with all earlier columns at once.  Two passes per column, and more while a
+// pass still takes away over half of the column: what is left of a column in
+// the span of the earlier ones is rounding noise, which has to be made
+// orthogonal in its turn (the columns of fewer than s nonzero singular
+// values; with two passes alone the noise stays in the span).  A column that
 // vanishes stays zero.  One block; every thread owns the same rows
 // f = tid + k * blockDim in every step.  red: (waves + 1) * kMaxS doubles.
+constexpr int kOrthPasses = 6;
+
 __device__ inline void gram_schmidt(int p, int s, double *Q, double *red) {
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   constexpr int NW = kOrthThreads / kWave;
   double *tot = red + NW * kMaxS;
   for (int j = 0; j < s; ++j) {
-    for (int pass = 0; pass < 3; ++pass) {  // two projections, then the norm
-      const int k0 = pass < 2 ? 0 : j, k1 = pass < 2 ? j : j + 1;
-      for (int g = k0; g < k1; g += 8) {
-        double d[8];
+    double nn = 0.0, before = 0.0;  // squared norm of the column, and one pass ago
+    for (int pass = 0;; ++pass) {
+      // with columns 0 .. j, from pass 2 on first the norm alone
+      const int k0 = pass < 2 ? 0 : j;
+      auto products = [&](int a, int b) {
+        for (int g = a; g < b; g += 8) {
+          double d[8];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) d[k] = 0.0;
-        for (int f = threadIdx.x; f < p; f += kOrthThreads) {
-          const double qj = Q[(size_t)f * s + j];
+          for (int k = 0; k < 8; ++k) d[k] = 0.0;
+          for (int f = threadIdx.x; f < p; f += kOrthThreads) {
+            const double qj = Q[(size_t)f * s + j];
 #pragma unroll
-          for (int k = 0; k < 8; ++k)
-            if (g + k < k1) d[k] = fma(Q[(size_t)f * s + g + k], qj, d[k]);
+            for (int k = 0; k < 8; ++k)
+              if (g + k < b) d[k] = fma(Q[(size_t)f * s + g + k], qj, d[k]);
+          }
+          const double t = wave_sum8_groups(d);
+          if ((lane & 7) == 0) red[wave * kMaxS + (g - a) + lane / 8] = t;
         }
-        const double t = wave_sum8_groups(d);
-        if ((lane & 7) == 0) red[wave * kMaxS + (g - k0) + lane / 8] = t;
-      }
-      __syncthreads();
-      if ((int)threadIdx.x < k1 - k0) {
-        double t = 0.0;
-        for (int w = 0; w < NW; ++w) t += red[w * kMaxS + threadIdx.x];
-        tot[threadIdx.x] = t;
-      }
-      __syncthreads();
-      if (pass < 2) {
-        for (int f = threadIdx.x; f < p; f += kOrthThreads) {
-          double qj = Q[(size_t)f * s + j];
-          for (int k = 0; k < j; ++k) qj = fma(-tot[k], Q[(size_t)f * s + k], qj);
-          Q[(size_t)f * s + j] = qj;
+        __syncthreads();
+        if ((int)threadIdx.x < b - a) {
+          double t = 0.0;
+          for (int w = 0; w < NW; ++w) t += red[w * kMaxS + threadIdx.x];
+          tot[a + threadIdx.x] = t;
         }
-      } else {
-        const double nn = tot[0];
-        const double inv = nn > 0.0 ? 1.0 / sqrt(nn) : 0.0;
-        for (int f = threadIdx.x; f < p; f += kOrthThreads) Q[(size_t)f * s + j] *= inv;
+        __syncthreads();
+      };
+      products(k0, j + 1);
+      nn = tot[j];
+      if (pass >= 2) {  // uniform
+        if (nn >= 0.25 * before || !(nn > 0.0) || pass == kOrthPasses) break;
+        products(0, j);
+      }
+      before = nn;
+      for (int f = threadIdx.x; f < p; f += kOrthThreads) {
+        double qj = Q[(size_t)f * s + j];
+        for (int k = 0; k < j; ++k) qj = fma(-tot[k], Q[(size_t)f * s + k], qj);
+        Q[(size_t)f * s + j] = qj;
       }
       __syncthreads();  // tot is read before the next pass writes it
     }
+    // still falling: nothing of it is outside the span (C^T reaches no further
+    // features than the earlier columns hold)
+    const double inv = nn > 0.0 && nn >= 0.25 * before ? 1.0 / sqrt(nn) : 0.0;
+    for (int f = threadIdx.x; f < p; f += kOrthThreads) Q[(size_t)f * s + j] *= inv;
+    __syncthreads();
   }
 }
 
