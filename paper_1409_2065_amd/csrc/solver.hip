@@ -2808,7 +2808,7 @@ static void free_launch_set(LaunchSet &L) {
 // vec_of[k] (64 * vec features per wave) and about ipw_of[k] items per wave
 // (waves with several items prefetch the next); point launches are grouped
 // by (vec, ipw), edge launches by each instance's features per lane (one_edge:
-// one launch for all).  Sets the problems' tile fields and scalar slot 0.
+// one launch for all).  Sets the problems' tile fields.
 constexpr int kBatchEdgeItems = 4;  // items per wave of the batched item edge sweep
 
 static cc_status build_launch_set(LaunchSet &L, const std::vector<Problem *> &probs,
@@ -2837,6 +2837,9 @@ static cc_status build_launch_set(LaunchSet &L, const std::vector<Problem *> &pr
     const Launch Li = edge_items_grid(P->n_items, P->eipw);
     pblocks[b] = Lp.blocks;
     eblocks[b] = Li.blocks;
+    // the tables run from slot 0, where a run puts the scalars first; until
+    // then they stay in the slot they are in
+    const int slot = P->slot;
     for (int par = 0; par < 2; ++par) {
       P->slot = par;
       PointArgs x = point_args(P, Lp);
@@ -2846,7 +2849,7 @@ static cc_status build_launch_set(LaunchSet &L, const std::vector<Problem *> &pr
       P->slot = par ^ 1;
       ea[par].push_back(edge_args(P, Li, 0, Lp.blocks));
     }
-    P->slot = 0;
+    P->slot = slot;
   }
   // classes (features per lane and items per wave of the point sweep,
   // features per lane of the edge sweep) in order of first appearance along
