@@ -2,14 +2,16 @@
 //
 // A problem whose gather copy, edge lists and q factors fit in the LDS of one
 // CU, and whose sweeps one CU does in less time than two kernel launches
-// take, is solved by one block that runs many iterations per launch: the two
+// take, is solved by one block that runs many iterations per launch: the
 // points of an iteration at which everything must be known (the new A, the
-// sums of d) are block barriers instead of kernel boundaries.  The gather
+// sums of d, the scalars they give) are three block barriers instead of kernel
+// boundaries.  The gather
 // copy is double-buffered in LDS, with the low half of A, the q factors, the
 // edges with their weights and norms, and the neighbour lists beside it.  A
-// sweep reads X and the mask from L2 (and U where entries are missing) while
-// it sums neighbours; only the windows of the stopping test and the state a
-// solve may end with are written.
+// sweep reads X and the mask from L2 while it sums neighbours; what is
+// written, beside the windows of the stopping test and the state a solve may
+// end with, is U where entries are missing, which every sweep reads and
+// writes.
 //
 // The arithmetic per point and edge is that of the sweeps over many blocks
 // (k_point, k_edge_items); the sums over points and over the features of an
@@ -20,7 +22,9 @@
 // and its LDS reads; the barriers, block sums and scalars take 2.4 us.
 // Measured per iteration, launches against this (mixed): 60 x 6 11.5 and
 // 3.7 us, 200 x 10 12.4 and 7.6, 200 x 24 12.8 and 10.2, 370 x 10 12.9 and
-// 10.8.  Blocks of 512 threads took 8 to 10% longer.
+// 10.8.  Blocks of 512 threads took 8 to 10% longer.  At 1024 threads (128
+// registers each) the mixed kernel spills 17 registers and the FP64 one 4 (56
+// and 20 bytes a lane), the FP32 one and all at 256 threads none.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -79,7 +79,8 @@ __global__ __launch_bounds__(kSlabNT) void k_point_slab(PointArgs a, SlabArgs sl
   const int nch = a.n * CPR;
   TG st[kSlabStage][4];
   // chunks k0 .. k0 + kSlabStage * NT - 1 of tile t (a chunk past the end or
-  // the row reads the first one and is not stored)
+  // the row reads the first one; past the end it is not stored, past the row
+  // its features are in the slab but no lane's sums are kept)
   auto stage_load = [&](int t, int k0) {
 #pragma unroll
     for (int u = 0; u < kSlabStage; ++u) {

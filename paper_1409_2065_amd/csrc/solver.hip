@@ -1048,7 +1048,8 @@ __global__ __launch_bounds__(kEdgeBlock) void k_edge_items_batch(const EdgeArgs 
 // each other on one stream, where a launch per width left most of the chip
 // idle in each (12 requests of four widths: 18.7 + 13.4 + 11.8 + 11.7 us, here
 // 24).  A batch's graph runs the widths as parallel chains instead, in
-// kernels that fit more waves per SIMD (48 instances: 29 us, here 33).
+// kernels that fit more waves per SIMD (48 instances: 29 us, here 33).  Held to
+// 128 registers the FP32 and mixed kernels spill 14 (28 bytes a lane).
 constexpr int kNvShift = 16;
 
 template <int PREC>
