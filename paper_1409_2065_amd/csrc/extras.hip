@@ -256,8 +256,6 @@ __device__ inline void gram_schmidt(int p, int s, double *Q, double *red) {
   for (int j = 0; j < s; ++j) {
     double nn = 0.0, before = 0.0;  // squared norm of the column, and one pass ago
     for (int pass = 0;; ++pass) {
-      // with columns 0 .. j, from pass 2 on first the norm alone
-      const int k0 = pass < 2 ? 0 : j;
       auto products = [&](int a, int b) {
         for (int g = a; g < b; g += 8) {
           double d[8];
@@ -280,8 +278,9 @@ __device__ inline void gram_schmidt(int p, int s, double *Q, double *red) {
         }
         __syncthreads();
       };
-      products(k0, j + 1);
-      nn = tot[j];
+      // the norm beside the products in pass 1, by itself first from then on
+      products(pass < 2 ? 0 : j, pass == 0 ? j : j + 1);
+      nn = pass == 0 ? 0.0 : tot[j];
       if (pass >= 2) {  // uniform
         if (nn >= 0.25 * before || !(nn > 0.0) || pass == kOrthPasses) break;
         products(0, j);
