@@ -1,6 +1,6 @@
 """Sampled timing of solves by one workgroup: every sample_every-th sweep of
 all that run, over solves of any length (a solve that reports I iterations
-runs sweeps 0..I, the last one's sums being its verdict)."""
+runs sweeps 0..I, whose last one's sums end it)."""
 import pytest
 import torch
 
